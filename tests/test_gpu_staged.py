@@ -118,3 +118,33 @@ def test_a_non_finite_weight_stays_in_its_row(torch_cuda, value):
     dXg, dWg = dX.cpu().numpy(), layer.dW.cpu().numpy()
     assert np.isnan(dXg[:, held]).all() and np.isfinite(dXg[:, ~held]).all()
     assert np.isnan(dWg[77]).all() and np.isfinite(np.delete(dWg, 77, axis=0)).all()
+
+
+@pytest.mark.parametrize("value", ["bf16", "f32"])
+@pytest.mark.parametrize("L,k", [(253, 16), (254, 11), (255, 3), (251, 17), (253, 32)])
+def test_rows_past_the_end_are_left_alone(torch_cuda, value, L, k):
+    """The layer's arrays are the leading L rows of larger ones: what lies past
+    them keeps its bits, in the stored-gradient and in the Adam mode (the last
+    unit of dW holds fewer rows than the others)."""
+    torch = torch_cuda
+    w = shape(value, L, 96, k, 33)
+    inp, bias = inputs(w, 8)
+    note("staged tail L=%d k=%d %s" % (L, k, value))
+    layer = make_gpu_layer(inp, w, bias_values=bias)
+    layer.close()
+    names = ["W", "I", "m", "v", "dW", "bias", "bias_m", "bias_v", "dbias"]
+    big = {}
+    for n in names:
+        t = getattr(layer, n)
+        big[n] = torch.full((L + 5,) + tuple(t.shape[1:]), 7, dtype=t.dtype, device=t.device)
+        big[n][:L] = t
+        setattr(layer, n, big[n][:L])
+    layer.bind(w.d)
+    X, off, lab = batch_to_gpu(inp.X, inp.off, inp.lab, w.value)
+    layer.dW.fill_(np.nan)
+    layer.backward(X, off, lab)
+    layer.train_step(X, off, lab, t=2)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(layer.dW).all())
+    for n in names:
+        assert bool((big[n][L:] == 7).all()), n
