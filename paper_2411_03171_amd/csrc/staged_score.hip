@@ -7,11 +7,16 @@
 // serve a row, a lane NP (bf16) or SPL (fp32) samples.  The next round of
 // indices and weights is in flight while the current one is gathered.
 //
-// Positives are rare (a few per sample), so the walk takes every (sample,
-// row) as a negative; afterwards each workgroup lists the positives of its own
-// rows and corrects them: it rescores them from the LDS tile, adds the
-// difference to the loss and rewrites g.
+// The targets are a bit per sample and row in LDS, for as many rows at a time
+// as the image leaves room for: the workgroup takes its rows in segments and
+// scans the batch's positives before each.  A label that repeats sets its bit
+// twice.  Positives are rare (a few per sample), so a wave whose four rows have
+// none takes the loss of a negative without looking at the bits.  (Taking every
+// pair as a negative and correcting the positives afterwards cannot give the
+// loss and the row sums of g their small values back: the terms of a positive
+// with a large score do not cancel to the last bit.)
 #include <algorithm>
+#include <type_traits>
 
 #include "gather_dev.h"
 
@@ -96,18 +101,6 @@ __device__ __forceinline__ void store_g(Rsrc rG, uint32_t row_elems, int q, bool
     }
 }
 
-// LDS byte offset of (column c, sample b) in the X image, and its value
-template <int VT, int NP>
-__device__ __forceinline__ float image_at(const unsigned char *xs, int c, int b) {
-    if constexpr (VT == FFSL_BF16) {
-        const int r = b / NP, p = (b % NP) ^ staged_swz_a(c, NP);
-        return bf16_bits_to_f32(
-            *reinterpret_cast<const uint16_t *>(xs + (size_t)c * (32 * NP) + 8 * (NP * (r >> 2) + p) + 2 * (r & 3)));
-    } else {
-        return *reinterpret_cast<const float *>(xs + (size_t)c * (64 * NP) + 4 * b);
-    }
-}
-
 // NP samples per lane; S planes of g (0: none); FULL: bf16 fan-ins that are a
 // multiple of 32 (unused for fp32)
 template <int VT, int NP, int S, bool FULL, bool IDX16>
@@ -123,14 +116,10 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
     const int d = a.d, k = a.k;
     const int tile = blockIdx.y, b0 = tile * BT, nb = min(BT, a.B - b0);
     const uint32_t image = (uint32_t)(d + 1) * COL;
-    // after the image: a list of positives (one per thread: row, sample, what it
-    // changes its g by), a count per wave
-    int32_t *row_s = reinterpret_cast<int32_t *>(st_smem + image);   // nthr + 64
-    int32_t *smp_s = row_s + nthr + 64;
-    float *dg_s = reinterpret_cast<float *>(smp_s + nthr);
-    float *dsum_s = reinterpret_cast<float *>(smp_s);   // once the samples are used
-    int32_t *cnt_s = reinterpret_cast<int32_t *>(dg_s + nthr);
-    float *red = reinterpret_cast<float *>(row_s);   // one loss sum per wave, at the end
+    // after the image: the targets of a segment of rows, a bit per sample
+    constexpr int YW = BT == 64 ? 2 : 1;             // words per row
+    uint32_t *ym = reinterpret_cast<uint32_t *>(st_smem + image);   // seg_rows * YW
+    float *red = reinterpret_cast<float *>(ym);      // one loss sum per wave, at the end
 
     const uint32_t r0 = blockIdx.x * a.rows_per_wg, r1 = min(a.rows, r0 + a.rows_per_wg);
     const Rsrc rI = make_rsrc(a.I, a.rows * (uint32_t)k * (a.idx16 ? 2u : 4u));
@@ -167,12 +156,28 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
         advance(l_nxt, rd_nxt);
     };
 
+    auto clear_targets = [&] {
+        for (uint32_t i = tid; i < a.seg_rows * YW; i += nthr) ym[i] = 0u;
+    };
+    uint32_t s0 = r0;   // first row of the segment
+    auto set_targets = [&](int2 first) {
+        const uint32_t n = min(a.seg_rows, r1 - s0);
+        for (int base = 0; base < a.nnz; base += nthr) {
+            int2 p = first;
+            if (base > 0) p = base + tid < a.nnz ? a.pos[base + tid] : make_int2(-1, 0);
+            const int64_t lr = (int64_t)p.x - a.row0 - s0;
+            const int b = p.y - b0;
+            if (lr >= 0 && lr < (int64_t)n && b >= 0 && b < nb) atomicOr(&ym[lr * YW + (b >> 5)], 1u << (b & 31));
+        }
+    };
+
     // the first positives and the next two rounds load while the tile is staged
-    int2 mypos = tid < a.nnz ? a.pos[tid] : make_int2(-1, 0);
+    const int2 mypos = tid < a.nnz ? a.pos[tid] : make_int2(-1, 0);
     Rd ra, rb;
     float ba, bb;
     load(ra, ba);
     load(rb, bb);
+    clear_targets();
     stage_image(a.xa + (size_t)tile * image, image, wave, lane, nwaves);
     __syncthreads();
 
@@ -183,6 +188,8 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
 
     auto process = [&](const Rd &o, float bias) {
         const int kr = k - 32 * rd_cur;
+        // the targets of the lane's samples
+        const uint32_t yw = ym[(l_cur + grp - s0) * YW + (BT == 64 ? q >> 3 : 0)];
         if constexpr (BF)
             tr_round<NP, FULL>(o, d, kr, q, pbase, z);
         else
@@ -216,14 +223,21 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
                         a.logits[(int64_t)(b0 + NP * q + e) * a.L + a.row0 + l] = zs[e];
             }
             float g[NP];
+            const uint32_t y = (yw >> (NP * q & 31)) & ((1u << NP) - 1u);
+            auto grads = [&](auto positives) {
 #pragma unroll
-            for (int e = 0; e < NP; ++e) {
-                const bool live = valid && NP * q + e < nb;
-                const LossGrad r = loss_grad(zs[e], false, a.hinge, a.s);
-                loss_acc += live ? r.loss : 0.f;
-                g[e] = live ? r.g : 0.f;
-                z[e] = 0.f;
-            }
+                for (int e = 0; e < NP; ++e) {
+                    const bool live = valid && NP * q + e < nb;
+                    const LossGrad r = loss_grad(zs[e], positives && ((y >> e) & 1u), a.hinge, a.s);
+                    loss_acc += live ? r.loss : 0.f;
+                    g[e] = live ? r.g : 0.f;
+                    z[e] = 0.f;
+                }
+            };
+            if (__builtin_amdgcn_ballot_w64(y != 0u) == 0)
+                grads(std::false_type{});
+            else
+                grads(std::true_type{});
             if constexpr (S > 0) {
                 store_g<NP, S>(rG, g_tile + l * (uint32_t)(S * BT), q, valid, a.nb_G, g);
                 float sg = 0.f;
@@ -236,92 +250,24 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
         advance(l_cur, rd_cur);
     };
 
-    while (l_cur < r1) {
-        process(ra, ba);
-        load(ra, ba);
-        if (l_cur >= r1) break;
-        process(rb, bb);
-        load(rb, bb);
-    }
-
-    // the positives of this workgroup's rows: listed in the batch's order, so
-    // that the loss sums in a fixed order, and taken by 16 lanes each
-    for (int base = 0; base < a.nnz; base += nthr) {
-        if (base > 0) mypos = base + tid < a.nnz ? a.pos[base + tid] : make_int2(-1, 0);
-        const int64_t lr = (int64_t)mypos.x - a.row0;
-        const bool mine = lr >= (int64_t)r0 && lr < (int64_t)r1 && mypos.y >= b0 && mypos.y < b0 + nb;
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(mine);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the walk's g is stored
-        __syncthreads();                                   // and the list is free
-        if (lane == 0) cnt_s[wave] = __builtin_popcountll(bal);
+    // a whole segment is an even number of steps for every wave, so that it
+    // ends on the same of the two rounds in flight
+    for (;;) {
+        set_targets(mypos);
         __syncthreads();
-        int at = 0, hits = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            const int cw = cnt_s[w];
-            at += w < wave ? cw : 0;
-            hits += cw;
+        const uint32_t s1 = min(r1, s0 + a.seg_rows);
+        while (l_cur < s1) {
+            process(ra, ba);
+            load(ra, ba);
+            if (l_cur >= s1) break;
+            process(rb, bb);
+            load(rb, bb);
         }
-        if (mine) {
-            const int h = at + __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-            row_s[h] = (int)lr;
-            smp_s[h] = mypos.y - b0;
-        }
+        s0 += a.seg_rows;
+        if (s0 >= r1) break;
         __syncthreads();
-        for (int h = tid >> 4; h < hits; h += nthr >> 4) {   // the same in all 16 lanes
-            const uint32_t l = (uint32_t)row_s[h];
-            const int smp = smp_s[h];
-            float zz = 0.f;
-            for (int j = q; j < k; j += 16) {
-                const uint32_t el = l * (uint32_t)k + j;
-                const int c = (int)(a.idx16 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rI, el * 2u, 0, 0)
-                                            : ld32(rI, el * 4u));
-                const float w = BF ? __uint_as_float((uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rW, el * 2u, 0, 0) << 16)
-                                   : ldf(rW, el * 4u);
-                zz = fmaf(w, image_at<VT, NP>(st_smem, clamp_col((uint32_t)c, d), smp), zz);
-            }
-            zz = sum16(zz) + ldf(rB, l * 4u);
-            if (q == 0) {
-                const LossGrad p1 = loss_grad(zz, true, a.hinge, a.s);
-                const LossGrad p0 = loss_grad(zz, false, a.hinge, a.s);
-                loss_acc += a.hinge ? p1.loss - p0.loss : -zz;   // BCE: the terms differ by z
-                if constexpr (S > 0) {
-                    uint16_t p[S];
-                    planes<S>(p1.g, p);
-#pragma unroll
-                    for (int pl = 0; pl < S; ++pl)
-                        __builtin_amdgcn_raw_buffer_store_b16(
-                            p[pl], rG, (g_tile + l * (uint32_t)(S * BT) + pl * BT + (uint32_t)smp) * 2u, 0, 0);
-                    dg_s[h] = p1.g - p0.g;
-                }
-            }
-        }
-        if constexpr (S > 0) {
-            // the changes of a row's g add to its sum: 16 lanes add up those of
-            // one positive's row, and every positive of a row stores the same sum
-            if (tid < 64) row_s[hits + tid] = -1;
-            __syncthreads();
-            for (int h0 = 0; h0 < hits; h0 += nthr >> 4) {
-                const int h = h0 + (tid >> 4);
-                const int row = h < hits ? row_s[h] : -2;
-                float t = 0.f;
-                for (int e = 4 * q; e < hits; e += 64) {
-                    const int4 r = *reinterpret_cast<const int4 *>(row_s + e);
-                    const float4 g = *reinterpret_cast<const float4 *>(dg_s + e);
-                    t += r.x == row ? g.x : 0.f;
-                    t += r.y == row ? g.y : 0.f;
-                    t += r.z == row ? g.z : 0.f;
-                    t += r.w == row ? g.w : 0.f;
-                }
-                t = sum16(t);
-                if (q == 0 && h < hits) dsum_s[h] = t;
-            }
-            __syncthreads();
-            const int row = tid < hits ? row_s[tid] : 0;
-            const float old = tid < hits ? ldf(rS, (s_tile + row) * 4u) : 0.f;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (tid < hits) stf(rS, (s_tile + row) * 4u, old + dsum_s[tid]);
-        }
+        clear_targets();
+        __syncthreads();
     }
 
     if (a.want_loss) {
@@ -529,13 +475,18 @@ int launch_score(const Layer &ly, const StagedPlan &p, ScoreArgs &a, int *nwg_ou
     // only where the rows feed them
     int waves = 16;
     while (waves > 4 && (int64_t)a.rows < (int64_t)ly.num_cu * 4 * waves) waves /= 2;
-    const size_t shm = (size_t)(ly.d + 1) * p.cola + (size_t)waves * 64 * 12 + 64 * 4 + 64;
-    const int occ = std::max(1, std::min(2, (int)(160 * 1024 / shm)));
+    const size_t image = (size_t)(ly.d + 1) * p.cola, lds = 160 * 1024;
+    const int occ = std::max(1, std::min(2, (int)(lds / (image + 12 * 1024))));
     int64_t nwg = std::min<int64_t>((int64_t)ly.num_cu * occ, (a.rows + 4 * waves - 1) / (4 * waves));
     nwg = std::min<int64_t>(nwg, ly.max_parts);
     const int64_t per = (a.rows + nwg - 1) / nwg;
     a.rows_per_wg = (uint32_t)((per + 4 * waves - 1) / (4 * waves) * (4 * waves));
     nwg = (a.rows + a.rows_per_wg - 1) / a.rows_per_wg;
+    // the targets of as many rows as fit: a multiple of two steps of every wave
+    const size_t per_row = p.BT == 64 ? 8 : 4, unit = 8 * waves;
+    const size_t want = (a.rows_per_wg + unit - 1) / unit * unit, room = (lds / occ - image) / per_row / unit * unit;
+    a.seg_rows = (uint32_t)std::min(want, room);
+    const size_t shm = image + a.seg_rows * per_row;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return fail(FFSL_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));

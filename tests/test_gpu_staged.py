@@ -148,3 +148,80 @@ def test_rows_past_the_end_are_left_alone(torch_cuda, value, L, k):
     assert bool(torch.isfinite(layer.dW).all())
     for n in names:
         assert bool((big[n][L:] == 7).all()), n
+
+
+# (value, L, d, k, B): every scoring tile, one and three planes of g, positives
+# of more rows than a segment of targets holds (the last two)
+SETTLED = [("bf16", 300, 64, 12, 33), ("bf16", 300, 768, 32, 70), ("bf16", 290, 96, 40, 9), ("bf16", 300, 400, 8, 24),
+           ("f32", 300, 64, 12, 33), ("f32", 311, 700, 40, 9), ("bf16", 600011, 1151, 2, 64), ("f32", 1300003, 2303, 2, 12)]
+
+
+def settled(case, hinge):
+    """Every pair far on its right side: column 0, held by every row, is +-c in
+    a sample and the row's weight there +-1; a row's positives are the samples
+    of its sign, all others negatives.  One pair in three is no target, so some
+    rows stay unsettled."""
+    value, L, d, k, B = case
+    w = shape(value, L, d, k, B)
+    rng = np.random.default_rng(12)
+    I = np.stack([np.zeros(L, np.int64)] + [1 + (rng.integers(0, d - 1, L) + j * ((d - 1) // k)) % (d - 1)
+                                            for j in range(k - 1)], axis=1).astype(np.int32)
+    Wv = rng.standard_normal((L, k)).astype(np.float32) * 1e-3
+    Wv[:, 0] = np.where(np.arange(L) % 2 == 0, 1.0, -1.0)
+    X = rng.standard_normal((B, d)).astype(np.float32)
+    c = 2.0 if hinge else 24.0
+    X[:, 0] = np.where(np.arange(B) % 3 == 0, c, -c)
+    bias = (rng.standard_normal(L) * 0.01).astype(np.float32)
+    rows = np.arange(L) if L < 1000 else np.concatenate([np.arange(200), rng.integers(0, L, 100), [L - 1]])
+    per = [np.unique(rows[Wv[rows, 0] * X[b, 0] > 0]) for b in range(B)]
+    if L >= 1000:   # elsewhere a row has no positive: give it negative scores only
+        quiet = np.ones(L, bool)
+        quiet[rows] = False
+        Wv[quiet, 0] = 0.0
+        bias[quiet] -= c
+    off = np.concatenate([[0], np.cumsum([len(p) for p in per])]).astype(np.int64)
+    lab = np.concatenate(per).astype(np.int32)
+    bits = (lambda a: synth.f32_to_bf16_bits(a)) if value == "bf16" else (lambda a: a)
+    inp = synth.dataclasses.replace(synth.make_layer_inputs(shape(value, 8, d, k, B), 1), X=bits(X), W=bits(Wv), I=I, off=off, lab=lab,
+                                    bias=bias)
+    return w, inp, bias
+
+
+@pytest.mark.parametrize("case", SETTLED, ids=["-".join(map(str, c)) for c in SETTLED])
+def test_settled_positives_leave_nothing(torch_cuda, case):
+    """Squared hinge past the margin everywhere: the loss and every gradient are
+    exactly zero, and a step leaves weights and biases as they are."""
+    torch = torch_cuda
+    from paper_2411_03171_amd import ffsl
+    w, inp, bias = settled(case, True)
+    note("staged settled hinge %s" % (case,))
+    layer, loss, dX, fwd, z = grads(torch, w, inp, bias, flags=ffsl.FFSL_LOSS_SQHINGE)
+    for t in (loss, fwd, layer.dW, layer.dbias, dX):
+        assert bool((t == 0).all())
+    X, off, lab = batch_to_gpu(inp.X, inp.off, inp.lab, w.value)
+    W0, b0 = layer.W.clone(), layer.bias.clone()
+    loss, dX = layer.train_step(X, off, lab, t=1, lr=1e-2, flags=ffsl.FFSL_LOSS_SQHINGE)
+    assert bool((loss == 0).all()) and bool((dX == 0).all())
+    assert torch.equal(layer.W, W0) and torch.equal(layer.bias, b0)
+
+
+@pytest.mark.parametrize("case", SETTLED, ids=["-".join(map(str, c)) for c in SETTLED])
+def test_loss_of_settled_positives(torch_cuda, case):
+    """BCE of pairs with |z| about 24 on the right side, some ten orders below the
+    scores: held to the relative error of exp at that z, a few units of z's last
+    place (2^-20 each, z being a sum of k terms)."""
+    w, inp, bias = settled(case, False)
+    note("staged settled BCE %s" % (case,))
+    layer, loss, dX, fwd, z = grads(torch_cuda, w, inp, bias)
+    if w.L < 1000:
+        zz = oracle_grads(w, inp, bias, 1.0 / w.B)["z"]
+    else:
+        zz = z.cpu().numpy().astype(np.float64)
+    y = np.zeros((w.B, w.L), bool)
+    for b in range(w.B):
+        y[b, inp.lab[inp.off[b]:inp.off[b + 1]]] = True
+    e = np.exp(-np.abs(zz))
+    assert (np.where(y, zz, -zz) > 20).all()
+    want = np.log1p(e).sum() / w.B
+    assert abs(fwd.cpu().numpy()[0] - want) <= 1e-5 * want
+    assert abs(loss.cpu().numpy()[0] - want) <= 1e-5 * want
