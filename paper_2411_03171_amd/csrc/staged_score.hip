@@ -362,8 +362,7 @@ __global__ void __launch_bounds__(256) k_staged_prep(const StagedPrepArgs a) {
         } else if (i >= npos) {
             a.zero[i - npos] = 0u;
         } else {
-            // a positive's sample is the last b with off[b] <= e; a label that
-            // repeats within the sample counts once
+            // a positive's sample is the last b with off[b] <= e
             const int e = (int)(i - nimg), lb = a.lab[e];
             int lo = 0, hi = a.B - 1;
             while (lo < hi) {
@@ -371,9 +370,7 @@ __global__ void __launch_bounds__(256) k_staged_prep(const StagedPrepArgs a) {
                 if (a.off[mid] <= e) lo = mid;
                 else hi = mid - 1;
             }
-            const int e0 = max(a.off[lo], 0);
-            bool ok = lb >= 0 && a.off[lo] <= e && e < a.off[lo + 1];
-            for (int p = e0; ok && p < e; ++p) ok = a.lab[p] != lb;
+            const bool ok = lb >= 0 && a.off[lo] <= e && e < a.off[lo + 1];
             a.pos[e] = make_int2(ok ? lb : -1, lo);
         }
     }

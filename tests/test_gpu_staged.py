@@ -225,3 +225,40 @@ def test_loss_of_settled_positives(torch_cuda, case):
     want = np.log1p(e).sum() / w.B
     assert abs(fwd.cpu().numpy()[0] - want) <= 1e-5 * want
     assert abs(loss.cpu().numpy()[0] - want) <= 1e-5 * want
+
+
+def test_positives_of_one_sample_cost_what_those_of_many_do(torch_cuda):
+    """100 thousand positives in one sample, against as many over all samples:
+    the preparation must not compare a sample's labels with each other (that
+    took hundreds of times as long).  And a label given twice counts once."""
+    torch = torch_cuda
+    L, B, n = 200003, 32, 100000
+    w = shape("bf16", L, 64, 4, B)
+    rng = np.random.default_rng(3)
+    inp, bias = inputs(w, 9)
+    lab = rng.permutation(L)[:n].astype(np.int32)
+    one = np.full(B + 1, n, np.int64)
+    one[0] = 0
+    many = np.linspace(0, n, B + 1).astype(np.int64)
+    layer = make_gpu_layer(inp, w, bias_values=bias, nnz_max=2 * n)
+
+    def run(off, lab):
+        X, offt, labt = batch_to_gpu(inp.X, off, lab, w.value)
+        ts = []
+        for _ in range(4):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            loss = layer.forward_loss(X, offt, labt)
+            e1.record()
+            torch.cuda.synchronize()
+            ts.append(e0.elapsed_time(e1))
+        return min(ts), loss.cpu().numpy()[0]
+
+    note("staged positives of one sample")
+    t_many, _ = run(many, lab)
+    t_one, loss_one = run(one, lab)
+    assert t_one < 5.0 * t_many, (t_one, t_many)
+    twice = np.concatenate([lab, lab[::-1]])
+    off2 = one * 2
+    _, loss_two = run(off2, twice)
+    assert loss_one == loss_two
