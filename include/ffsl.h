@@ -109,8 +109,8 @@ FFSL_API size_t ffsl_workspace_bytes(int64_t L, int32_t d, int32_t k, int32_t B_
  * 128 up to 2048 and L < 2^24), so
  * an fp32 layer, or a bf16 layer off those shapes, needs only the partial sums,
  * the batch images and the gradients of a slab.
- * ffsl_workspace_bytes is this call with FFSL_BF16 (an upper bound for both
- * types).  Returns 0 for invalid shapes or types. */
+ * ffsl_workspace_bytes is the larger of this call with FFSL_BF16 and with
+ * FFSL_F32 (an upper bound for both types).  Returns 0 for invalid shapes or types. */
 FFSL_API size_t ffsl_workspace_bytes_ex(int64_t L, int32_t d, int32_t k, int32_t value_dtype,
                             int32_t B_max, int32_t nnz_max);
 

@@ -185,9 +185,10 @@ size_t ffsl_workspace_bytes_ex(int64_t L, int32_t d, int32_t k, int32_t value_dt
 }
 
 size_t ffsl_workspace_bytes(int64_t L, int32_t d, int32_t k, int32_t B_max, int32_t nnz_max) {
-    // without the value type: the bf16 layout, which holds every buffer an
-    // fp32 layer of the same shape needs
-    return ffsl_workspace_bytes_ex(L, d, k, FFSL_BF16, B_max, nnz_max);
+    // without the value type: bf16 layouts hold the fast paths' buffers, fp32
+    // layouts the wider images of the batch
+    return std::max(ffsl_workspace_bytes_ex(L, d, k, FFSL_BF16, B_max, nnz_max),
+                    ffsl_workspace_bytes_ex(L, d, k, FFSL_F32, B_max, nnz_max));
 }
 
 int ffsl_create_layer_ex(ffsl_layer **out, int64_t L, int32_t d, int32_t k, int32_t value_dtype,

@@ -315,7 +315,7 @@ def test_workspace_carries_only_what_the_path_uses(torch_cuda):
     carry = 4 * (L * 32 + L)
     assert bf16 >= f32 + carry
     assert off_path < f32 and f32 < carry
-    # the call without a type is the bf16 layout (an upper bound for both)
+    # the call without a type is the larger of the two: here the bf16 layout
     assert lib.ffsl_workspace_bytes(L, 768, 32, B, nnz) == bf16
     assert lib.ffsl_workspace_bytes_ex(L, 768, 32, 9, B, nnz) == 0
 
