@@ -550,7 +550,6 @@ static int launch_staged(const SweepCall &c, const WsLayout &wl) {
             wa.tilesw = p.tilesw;
             wa.adam_on = c.mode == SWEEP_FUSED;
             wa.adam = c.adam;
-            wa.dx0 = want_dx ? dx_part : nullptr;
             rc = launch_dw(ly, p, wa, c.stream);
             if (rc) return rc;
         }

@@ -263,3 +263,69 @@ def test_positives_of_one_sample_cost_what_those_of_many_do(torch_cuda):
     off2 = one * 2
     _, loss_two = run(off2, twice)
     assert loss_one == loss_two
+
+
+def plain_grads(w, inp, bias, hinge):
+    """z, g, dW, dbias and dX term by term in float64, with the infinities and
+    NaNs that the terms and sums give."""
+    X, W = values_f64(inp.X, w.value), values_f64(inp.W, w.value)
+    y = np.zeros((w.B, w.L), bool)
+    for b in range(w.B):
+        y[b, inp.lab[inp.off[b]:inp.off[b + 1]]] = True
+    with np.errstate(all="ignore"):
+        Xg = X[:, inp.I]                                     # [B, L, k]
+        z = (Xg * W[None]).sum(2) + bias[None].astype(np.float64)
+        if hinge:
+            yh = np.where(y, 1.0, -1.0)
+            g = -2.0 * yh * np.fmax(1.0 - yh * z, 0.0) / w.B
+        else:
+            e = np.exp(-np.abs(z))
+            g = (np.where(z >= 0, 1.0 / (1.0 + e), e / (1.0 + e)) - y) / w.B
+        dW = (g[:, :, None] * Xg).sum(0)
+        dX = np.zeros((w.B, w.d))
+        for b in range(w.B):
+            np.add.at(dX[b], inp.I, g[b][:, None] * W)
+    return z, g, dW, g.sum(0), dX
+
+
+def same_with_infinities(got, ref, rtol, what):
+    got, ref = np.asarray(got, np.float64), np.asarray(ref, np.float64)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), what
+    inf = np.isinf(ref)
+    assert np.array_equal(got[inf], ref[inf]), what
+    fin = np.isfinite(ref)
+    assert_close(got[fin], ref[fin], rtol, what)
+
+
+# an infinite weight: one, and one and three planes of g, in the stored-gradient
+# and in the Adam mode (whose dX is that of the weights before the update)
+INF = [("bf16", 200, 160, 16, 70, False, False), ("f32", 200, 160, 16, 70, False, False),
+       ("bf16", 133, 768, 32, 70, True, True), ("bf16", 133, 300, 100, 20, False, True)]
+
+
+@pytest.mark.parametrize("case", INF, ids=["-".join(map(str, c)) for c in INF])
+def test_infinite_weight(torch_cuda, case):
+    """An infinite weight makes its row's scores infinite of either sign, and the
+    terms of dX that hold it, or an infinite g, infinite or NaN; nothing else."""
+    value, L, d, k, B, hinge, fused = case
+    from paper_2411_03171_amd import ffsl
+    w = shape(value, L, d, k, B)
+    inp, bias = inputs(w, 6)
+    Wb = inp.W.copy()
+    Wb[77, 3] = np.inf if value == "f32" else 0x7F80
+    inp = synth.dataclasses.replace(inp, W=Wb)
+    note("staged infinite weight %s" % (case,))
+    flags = ffsl.FFSL_LOSS_SQHINGE if hinge else 0
+    layer = make_gpu_layer(inp, w, bias_values=bias)
+    X, off, lab = batch_to_gpu(inp.X, inp.off, inp.lab, w.value)
+    if fused:
+        _, dX = layer.train_step(X, off, lab, t=1, flags=flags)
+    else:
+        dX = layer.backward(X, off, lab, flags=flags)
+    z, g, dW, db, dXr = plain_grads(w, inp, bias, hinge)
+    assert np.isinf(z[:, 77]).all() and (z[:, 77] > 0).any() and (z[:, 77] < 0).any()
+    one_plane = fused and k in (32, 64)
+    same_with_infinities(dX.cpu().numpy(), dXr, 2e-2 if one_plane else RTOL_F32, "dX")
+    if not fused:
+        same_with_infinities(layer.dW.cpu().numpy(), dW, RTOL_F32, "dW")
+        same_with_infinities(layer.dbias.cpu().numpy(), db, RTOL_F32, "dbias")
