@@ -63,12 +63,18 @@ __device__ __forceinline__ LossGrad loss_grad(float z, bool y, int hinge, float 
 }
 
 // g as bf16 planes: each takes the leading 8 significant bits of what is left
-// (exact: three planes hold the 24 bits of an fp32); one plane is rounded
-template <int S>
+// (exact: three planes hold the 24 bits of an fp32); one plane is rounded.  A
+// non-finite g (ODD: there may be one) is all in the first plane.
+template <int S, bool ODD>
 __device__ __forceinline__ void planes(float g, uint16_t (&p)[S > 0 ? S : 1]) {
     if constexpr (S == 1) {
         p[0] = (uint16_t)(pack_bf16(g, 0.f) & 0xffffu);
     } else if constexpr (S == 3) {
+        if (ODD && (__float_as_uint(g) & 0x7f800000u) == 0x7f800000u) {
+            p[0] = f32_to_bf16_bits(g);
+            p[1] = p[2] = 0;
+            return;
+        }
         const uint32_t h = __float_as_uint(g) & 0xffff0000u;
         const float r1 = g - __uint_as_float(h);
         const uint32_t m = __float_as_uint(r1) & 0xffff0000u;
@@ -80,12 +86,12 @@ __device__ __forceinline__ void planes(float g, uint16_t (&p)[S > 0 ? S : 1]) {
 }
 
 // store the NP consecutive samples NP q .. of row l of every plane
-template <int NP, int S>
+template <int NP, int S, bool ODD>
 __device__ __forceinline__ void store_g(Rsrc rG, uint32_t row_elems, int q, bool ok, uint32_t nb_G, const float (&g)[NP]) {
     constexpr uint32_t BT = 16u * NP;
     uint16_t p[NP][S];
 #pragma unroll
-    for (int e = 0; e < NP; ++e) planes<S>(g[e], p[e]);
+    for (int e = 0; e < NP; ++e) planes<S, ODD>(g[e], p[e]);
 #pragma unroll
     for (int pl = 0; pl < S; ++pl) {
         const uint32_t o = ok ? (row_elems + pl * BT + (uint32_t)(NP * q)) * 2u : nb_G;
@@ -189,7 +195,8 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
     auto process = [&](const Rd &o, float bias) {
         const int kr = k - 32 * rd_cur;
         // the targets of the lane's samples
-        const uint32_t yw = ym[(l_cur + grp - s0) * YW + (BT == 64 ? q >> 3 : 0)];
+        uint32_t yw = 0u;
+        if (rd_cur == rounds - 1) yw = ym[(l_cur + grp - s0) * YW + (BT == 64 ? q >> 3 : 0)];
         if constexpr (BF)
             tr_round<NP, FULL>(o, d, kr, q, pbase, z);
         else
@@ -222,30 +229,39 @@ __global__ void __launch_bounds__(SC_MAX_THREADS) k_score(const ScoreArgs a) {
                     if (valid && NP * q + e < nb)
                         a.logits[(int64_t)(b0 + NP * q + e) * a.L + a.row0 + l] = zs[e];
             }
-            float g[NP];
+            // every pair as a negative; where one is a positive or has a g that is
+            // not finite, the wave's pairs once more
             const uint32_t y = (yw >> (NP * q & 31)) & ((1u << NP) - 1u);
-            auto grads = [&](auto positives) {
+            float g[NP], sg, ls;
+            auto grads = [&](auto odd) {
+                sg = ls = 0.f;
 #pragma unroll
                 for (int e = 0; e < NP; ++e) {
                     const bool live = valid && NP * q + e < nb;
-                    const LossGrad r = loss_grad(zs[e], positives && ((y >> e) & 1u), a.hinge, a.s);
-                    loss_acc += live ? r.loss : 0.f;
+                    const LossGrad r = loss_grad(zs[e], odd && ((y >> e) & 1u), a.hinge, a.s);
+                    ls += live ? r.loss : 0.f;
                     g[e] = live ? r.g : 0.f;
-                    z[e] = 0.f;
+                    sg += g[e];
                 }
             };
-            if (__builtin_amdgcn_ballot_w64(y != 0u) == 0)
-                grads(std::false_type{});
-            else
+            auto store = [&](auto odd) {
+                if constexpr (S > 0)
+                    store_g<NP, S, decltype(odd)::value>(rG, g_tile + l * (uint32_t)(S * BT), q, valid, a.nb_G, g);
+            };
+            grads(std::false_type{});
+            if (__builtin_amdgcn_ballot_w64(y != 0u || (S == 3 && (__float_as_uint(sg) & 0x7f800000u) == 0x7f800000u)) == 0) {
+                store(std::false_type{});
+            } else {
                 grads(std::true_type{});
+                store(std::true_type{});
+            }
+            loss_acc += ls;
             if constexpr (S > 0) {
-                store_g<NP, S>(rG, g_tile + l * (uint32_t)(S * BT), q, valid, a.nb_G, g);
-                float sg = 0.f;
-#pragma unroll
-                for (int e = 0; e < NP; ++e) sg += g[e];
                 sg = sum16(sg);
                 stf(rS, valid && q == 0 ? (s_tile + l) * 4u : 0xfffffff0u, sg);
             }
+#pragma unroll
+            for (int e = 0; e < NP; ++e) z[e] = 0.f;
         }
         advance(l_cur, rd_cur);
     };
@@ -332,10 +348,15 @@ __device__ __forceinline__ uint4 image_b_word(const StagedPrepArgs &a, int tile,
             if constexpr (VT == FFSL_BF16) {
                 x = static_cast<const uint16_t *>(a.X)[(size_t)b * a.d + c];
             } else {
-                // plane pl of the value's three bf16 planes (exact)
+                // plane pl of the value's three bf16 planes (exact; a non-finite
+                // value is all in the first)
                 float f = static_cast<const float *>(a.X)[(size_t)b * a.d + c];
-                for (int t = 0; t < pl; ++t) f -= __uint_as_float(__float_as_uint(f) & 0xffff0000u);
-                x = __float_as_uint(f) >> 16;
+                if ((__float_as_uint(f) & 0x7f800000u) == 0x7f800000u) {
+                    x = pl == 0 ? f32_to_bf16_bits(f) : 0u;
+                } else {
+                    for (int t = 0; t < pl; ++t) f -= __uint_as_float(__float_as_uint(f) & 0xffff0000u);
+                    x = __float_as_uint(f) >> 16;
+                }
             }
         }
         o[i >> 1] |= x << (16 * (i & 1));
