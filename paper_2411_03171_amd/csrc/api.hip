@@ -1,4 +1,5 @@
 // C ABI of libffsl: argument validation, workspace layout, dispatch.
+#include <float.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -138,6 +139,14 @@ static int check_adam(int64_t t, float lr, float b1, float b2, float eps, float 
     p->bc1 = (float)(1.0 - pow((double)b1, (double)t));
     p->bc2 = (float)(1.0 - pow((double)b2, (double)t));
     if (!(p->bc1 > 0.f) || !(p->bc2 > 0.f)) return fail(FFSL_EINVAL, "bias correction underflows");
+    const auto pair = [](double x, float *hi, float *lo) {
+        *hi = (float)x;
+        if (fabs((double)*hi) > fabs(x)) *hi = nextafterf(*hi, 0.f);
+        *lo = (float)(x - (double)*hi);
+        if (x != 0.0 && *lo == 0.f) *lo = copysignf(FLT_MIN, (float)x);
+    };
+    pair((double)lr / (double)p->bc1, &p->c1, &p->c1_lo);
+    pair(1.0 / (double)p->bc2, &p->c2, &p->c2_lo);
     return FFSL_OK;
 }
 

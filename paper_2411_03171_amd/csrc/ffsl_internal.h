@@ -109,6 +109,10 @@ template <> struct ValueT<FFSL_BF16> {
 struct AdamParams {
     float lr, b1, b2, eps, wd;
     float bc1, bc2;   // 1 - b1^t, 1 - b2^t (computed in double on the host)
+    // lr / bc1 and 1 / bc2, each as a pair that adds up to it: the first part
+    // cut towards zero, the second of the same sign and never zero (but for lr =
+    // 0), so that an infinite moment times the pair stays infinite
+    float c1, c1_lo, c2, c2_lo;
 };
 
 enum SweepMode { SWEEP_FWD = 0, SWEEP_BWD = 1, SWEEP_FUSED = 2 };

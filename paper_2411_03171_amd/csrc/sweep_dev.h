@@ -187,6 +187,22 @@ __device__ __forceinline__ float adam_step(float p, float g, float &mm, float &v
     return fmaf(-((lr * inv_bc1) * mm), __builtin_amdgcn_rcpf(den), p);
 }
 
+// Adam with every operation rounded about once, as correctly rounded divides
+// and a root would: constants as pairs (AdamConsts), the root and the quotient
+// of the hardware's approximations corrected by their remainders.  rsq is 0 or
+// infinite at the ends (the root of 0 and infinity is the value itself), and a
+// quotient by infinity has no remainder: there the corrections are NaN and what
+// they correct stands.
+__device__ __forceinline__ float adam_fine(float p, float g, float &mm, float &vv, const AdamParams &ap, float decay) {
+    mm = fmaf(ap.b1, mm, (1.f - ap.b1) * g);
+    vv = fmaf(ap.b2, vv, ((1.f - ap.b2) * g) * g);
+    const float n = fmaf(mm, ap.c1, mm * ap.c1_lo), x = fmaf(vv, ap.c2, vv * ap.c2_lo);
+    const float y = __builtin_amdgcn_rsqf(x), s0 = x * y;
+    const float s1 = fmaf(fmaf(-s0, s0, x), 0.5f * y, s0), den = (s1 == s1 ? s1 : x) + ap.eps;
+    const float r = __builtin_amdgcn_rcpf(den), q0 = n * r, q1 = fmaf(fmaf(-den, q0, n), r, q0);
+    return fmaf(p, decay, -(q1 == q1 ? q1 : q0));
+}
+
 // Regrowth draws of SET: Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11)
 // keyed by (seed, SET_KEY_HI) and counted by (row, set_round, attempt / 4, 0).
 constexpr uint64_t SET_KEY_HI = 0x5345545F52454752ull;  // "SET_REGR"

@@ -341,3 +341,47 @@ def test_infinities(torch_cuda, case, where):
     if not fused:
         same_with_infinities(layer.dW.cpu().numpy(), dW, RTOL_F32, "dW")
         same_with_infinities(layer.dbias.cpu().numpy(), db, RTOL_F32, "dbias")
+
+
+@pytest.mark.parametrize("case", [("f32", 30001, 256, 32, 32), ("f32", 4001, 700, 100, 40)], ids=lambda c: "-".join(map(str, c)))
+def test_adam_of_the_step_rounds_each_weight_once(torch_cuda, case):
+    """The stored weight against float64 Adam on the stored moments, in units of
+    its last place: one rounding is uniform in +-1/2, a mean square of 1/12, to
+    which the roundings of the update add little where it is far below the weight
+    (a product rounded before the sum makes it 1/6).  And an update from zero is
+    as exact as divides and a root that each round correctly: the roundings of
+    lr m / bc1, v / bc2 (halved by the root), the root, the sum with eps and the
+    quotient are 2.25 units of 2^-23 at most, and 1/3 of that in the mean square
+    (0.38 when all five are uniform)."""
+    torch = torch_cuda
+    value, L, d, k, B = case
+    w = shape(value, L, d, k, B)
+    inp, _ = inputs(w, 11)
+    rng = np.random.default_rng(11)
+    lr, wd, eps = 1e-4, 1e-3, 1e-8
+    for zero in (False, True):
+        for t in (3, 1000):
+            note("staged Adam %s zero=%s t=%d" % (case, zero, t))
+            layer = make_gpu_layer(synth.dataclasses.replace(inp, W=np.zeros_like(inp.W)) if zero else inp, w,
+                                   bias_values=np.zeros(L, np.float32), unfused=False)
+            layer.m.copy_(torch.from_numpy((rng.standard_normal((L, k)) * 1e-4).astype(np.float32)))
+            layer.v.copy_(torch.from_numpy((rng.random((L, k)) * 1e-7).astype(np.float32)))
+            W0 = layer.W.double().cpu().numpy()
+            X, off, lab = batch_to_gpu(inp.X, inp.off, inp.lab, w.value)
+            layer.train_step(X, off, lab, t=t, lr=lr, wd=wd, eps=eps)
+            f = lambda x: float(np.float32(x))
+            bc1, bc2 = f(1 - f(0.9) ** t), f(1 - f(0.999) ** t)
+            m, v = layer.m.double().cpu().numpy(), layer.v.double().cpu().numpy()
+            upd = f(lr) * (m / bc1) / (np.sqrt(v / bc2) + f(eps))
+            decay = f(np.float32(1) - np.float32(lr) * np.float32(wd))
+            ref = W0 * decay - upd
+            got = layer.W.double().cpu().numpy()
+            if zero:
+                rel = np.abs(got - ref) / np.abs(upd)
+                assert rel.max() <= 2.25 * 2.0 ** -23
+                assert np.sqrt((rel ** 2).mean()) <= 0.75 * 2.0 ** -23
+            else:
+                far = np.abs(ref) > 64 * np.abs(upd)
+                assert far.mean() > 0.05
+                ulp = np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
+                assert (((got - ref) / ulp)[far] ** 2).mean() <= 1.1 / 12
