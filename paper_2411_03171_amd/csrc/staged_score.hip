@@ -424,10 +424,11 @@ size_t staged_xa_bytes(int32_t d, int32_t vt, int32_t B_max) {
 size_t staged_xb_bytes(int32_t d, int32_t vt, int32_t B_max) {
     return al256((size_t)(B_max + 63) * (size_t)d * (vt == FFSL_BF16 ? 2 : 8));
 }
-// G holds at least one step of rows for the largest batch
+// G holds at least one step of rows for the largest batch, and STAGED_G_MAX
+// bytes in full
 size_t staged_g_bytes(int64_t L, int32_t B_max) {
     const int64_t per_row = (int64_t)(B_max + 63) * 3 * 2, rows = (L + 63) / 64 * 64;
-    return al256((size_t)std::min<int64_t>(rows, std::max<int64_t>(STAGED_G_MAX / per_row, 64)) * (size_t)per_row);
+    return al256((size_t)std::min<int64_t>(rows, std::max<int64_t>((STAGED_G_MAX + per_row - 1) / per_row, 64)) * (size_t)per_row);
 }
 
 // a sum per (tile, row) of G, whose tiles hold 16 samples and one plane at least
@@ -453,9 +454,13 @@ StagedPlan staged_plan(const Layer &ly, int B, int S, size_t g_bytes) {
     p.S = S;
     p.cola = BT * (bf ? 2 : 4);
     p.colb = bf ? 2 * p.BTW : p.BTW == 32 ? 192 : p.BTW == 16 ? 128 : 64;
-    int64_t slab = STAGED_SLAB_ROWS;
-    if (S > 0) slab = std::min<int64_t>(slab, (int64_t)(g_bytes / ((size_t)p.tiles * BT * S * 2)) / 64 * 64);
-    p.slab = std::min<int64_t>(slab, (ly.L + 63) / 64 * 64);
+    int64_t most_rows = STAGED_SLAB_ROWS;
+    if (S > 0) most_rows = std::min<int64_t>(most_rows, (int64_t)(g_bytes / ((size_t)p.tiles * BT * S * 2)) / 64 * 64);
+    // slabs of equal size: a small remainder costs three launches that each stage
+    // their image again (about 52 us of a step of 1048576 rows, fan-in 64, d 2048,
+    // B 128, whose third slab had 128 rows)
+    const int64_t slabs = (ly.L + most_rows - 1) / most_rows;
+    p.slab = ((ly.L + slabs - 1) / slabs + 63) / 64 * 64;
     return p;
 }
 

@@ -9,8 +9,8 @@ import numpy as np
 import pytest
 
 from paper_2411_03171_amd import synth
-from tests.parity import RTOL_F32, assert_close, batch_to_gpu, make_gpu_layer, note, values_f64
-from tests.test_gpu_layer import oracle_grads, torch_cuda  # noqa: F401  (fixture)
+from tests.parity import RTOL_F32, assert_close, batch_to_gpu, from_torch_bits, make_gpu_layer, note, values_f64
+from tests.test_gpu_layer import adam_reference, oracle_grads, torch_cuda  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -385,3 +385,32 @@ def test_adam_of_the_step_rounds_each_weight_once(torch_cuda, case):
                 assert far.mean() > 0.05
                 ulp = np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
                 assert (((got - ref) / ulp)[far] ** 2).mean() <= 1.1 / 12
+
+
+@pytest.mark.parametrize("case", [("bf16", 22003, 150, 100, 1024), ("bf16", 43011, 40, 12, 1024), ("f32", 22003, 128, 70, 1024),
+                                  ("f32", 43011, 64, 7, 1024)], ids=lambda c: "-".join(map(str, c)))
+def test_fused_step_over_several_slabs(torch_cuda, case):
+    """The fused step over two and three slabs and many batch tiles, with three
+    planes of g, at fan-ins of four rows and of half a row a unit."""
+    torch = torch_cuda
+    w = shape(*case)
+    inp, bias = inputs(w, 13)
+    s, t, lr = 1.0 / w.B, 3, 1e-2
+    rng = np.random.default_rng(13)
+    m0 = (rng.standard_normal((w.L, w.k)) * 1e-3).astype(np.float32)
+    v0 = ((0.5 + rng.random((w.L, w.k))) * 1e-5).astype(np.float32)
+    note("staged fused slabs %s" % (case,))
+    layer = make_gpu_layer(inp, w, bias_values=bias, unfused=False)
+    layer.m.copy_(torch.from_numpy(m0))
+    layer.v.copy_(torch.from_numpy(v0))
+    X, off, lab = batch_to_gpu(inp.X, inp.off, inp.lab, w.value)
+    loss, dX = layer.train_step(X, off, lab, t=t, s=s, lr=lr)
+    torch.cuda.synchronize()
+    r, Wn, mn, vn, bn, _, _ = adam_reference(w, inp, bias, s, t=t, lr=lr, m0=m0.astype(np.float64), v0=v0.astype(np.float64))
+    assert_close(loss.cpu().numpy()[0], r["loss"], RTOL_F32, "loss")
+    assert_close(dX.cpu().numpy(), r["dX"], RTOL_F32, "dX")
+    assert_close(layer.m.cpu().numpy(), mn, RTOL_F32, "m")
+    assert_close(layer.v.cpu().numpy(), vn, 2 * RTOL_F32, "v")   # the square of a gradient
+    assert_close(layer.bias.cpu().numpy(), bn, RTOL_F32, "bias")
+    Wg = values_f64(from_torch_bits(layer.W, w.value), w.value)
+    assert_close(Wg, Wn, RTOL_F32 if w.value == "f32" else 2.0 ** -8, "W")   # bf16: half an ulp
