@@ -89,11 +89,13 @@ FFSL_API int ffsl_version(void);
 
 /* Bytes of device workspace a layer of this shape needs for batches of up to
  * B_max samples with up to nnz_max positive (sample, label) pairs per batch.
- * Besides per-workgroup partial sums of the loss and dX (O(B_max * d)), the
- * fused step of fan-in-32 layers (d a multiple of 128 up to 768, 2^18 < L <
- * 2^25) carries dW and dbias between passes of 64 samples in 4*(L*k + L) bytes
- * when B_max > 64.  The fan-in-32 shapes also hold a list of up to L row numbers
- * (4*(L + 1) bytes) for ffsl_train_step_set.
+ * Besides per-workgroup partial sums of the loss and dX (O(B_max * d)), two
+ * kinds of fused step carry dW and dbias between passes over the batch, in
+ * 4*(L*k + L) bytes: fan-in 32 (d a multiple of 128 up to 768, 2^18 < L < 2^25)
+ * when B_max > 64, and fan-in 64 (d a multiple of 128 up to 2048, L < 2^24) when
+ * B_max > 16 and L*d >= 2^30, or B_max > 32, d > 1151 and L*d >= 2^29.  The
+ * fan-in-32 shapes also hold a list of up to L row numbers (4*(L + 1) bytes) for
+ * ffsl_train_step_set.
  * The other fused steps and the unfused calls keep two images of the batch (up
  * to 12 bytes per input) and the loss gradients of a slab of rows (up to 6
  * bytes per sample and row, and 4 bytes per 16 samples and row; 144 MiB at

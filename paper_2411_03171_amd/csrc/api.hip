@@ -55,9 +55,9 @@ WsLayout ws_layout(int64_t L, int32_t d, int32_t k, int32_t vt, int32_t B_max, i
     const bool bf16 = vt == FFSL_BF16;
     const bool wide = bf16 && wide_shape(L, d, k);
     const bool mx = bf16 && !wide && mx_shape(L, d, k);
-    // the wide path takes batches of one pass only
+    const bool wide_carry = wide && wide_carries(L, d, B_max);
     const int pass_b = wide ? WD_PASS_B : MX_PASS_B;
-    const int passes = wide ? 1 : (B_max + pass_b - 1) / pass_b;
+    const int passes = wide && !wide_carry ? 1 : std::min(wide ? WD_PASSES : 1 << 30, (B_max + pass_b - 1) / pass_b);
     size_t off = 0;
     // one partial per workgroup and batch tile (the narrowest tile is 16)
     w.loss_part = off;
@@ -66,7 +66,7 @@ WsLayout ws_layout(int64_t L, int32_t d, int32_t k, int32_t vt, int32_t B_max, i
     off = align256(off + sizeof(int32_t) * (size_t)std::max(nnz_max, 1));
     w.dx_part = off;
     off = align256(off + sizeof(float) * (size_t)max_parts * (size_t)B_max * (size_t)d);
-    w.has_partial = mx && B_max > MX_PASS_B && L >= MX_PASSES_MIN_L;
+    w.has_partial = wide_carry || (mx && B_max > MX_PASS_B && L >= MX_PASSES_MIN_L);
     w.dwp = off;
     if (w.has_partial) off = align256(off + sizeof(float) * (size_t)L * (size_t)k);
     w.dbp = off;

@@ -32,7 +32,7 @@ struct WsLayout {
     size_t tgt_b;       // int32 [nnz_max]  sample of each positive pair
     size_t dx_part;     // float [max_parts][B_max][d]
     size_t dwp, dbp;    // float [L][k], [L]: dW / dbias carried between the
-                        // batch passes of the fan-in-32 fast path (B_max > 64)
+                        // batch passes of a fused fast path
     size_t keys;        // uint32 [passes][1024]: each pass's sorted positives
     size_t xt;          // bf16 [passes][d][pass width]: the batch transposed per pass
     size_t set_list;    // int32 [1 + L]: the rows the fused step+SET sweep left
@@ -51,7 +51,8 @@ struct WsLayout {
 WsLayout ws_layout(int64_t L, int32_t d, int32_t k, int32_t vt, int32_t B_max, int32_t nnz_max, int max_parts);
 // samples per pass of the fused fast path
 constexpr int MX_PASS_B = 64;   // samples per pass of the fan-in-32 fast path
-constexpr int WD_PASS_B = 16;   // largest batch of the wide fan-in-64 fast path
+constexpr int WD_PASS_B = 16;   // samples per pass of the wide fan-in-64 fast path
+constexpr int WD_PASSES = 3;    // passes it takes at most
 // The fan-in-32 path takes larger batches in passes, each of which pays for its
 // own staging, first chunk and dX partial (about 50 us) but moves no loss
 // gradients through memory: below this many rows the staged sweep is faster
@@ -61,6 +62,25 @@ constexpr int64_t MX_PASSES_MIN_L = ((int64_t)1 << 18) + 1;
 // layers whose shape the wide fan-in-64 fast path serves (bf16 values)
 inline bool wide_shape(int64_t L, int32_t d, int32_t k) {
     return k == 64 && d % 128 == 0 && d >= 128 && d <= 2048 && L < ((int64_t)1 << 24);
+}
+// The batches it takes: one pass always; two or three where the layer is so
+// large that the staged sweep, which reads the rows once per kernel, tile and
+// column slice, loses more on them than a pass does (about 400 us a million
+// rows).  Staged time over passes' time, fan-in 64, at 2^18, 2^19 and 2^20 rows:
+//   B 17   d 768: 0.81 0.83 0.89   d 1024: 0.88 0.96 1.03   d 1536: 0.89 0.96 1.02   d 2048: 1.00 1.08 1.17
+//   B 48   d 768: 0.70 0.72 0.74   d 1024: 0.75 0.80 0.84   d 1536: 0.95 1.00 1.06   d 2048: 1.03 1.10 1.18
+// B 24 and 32 are within 0.03 of 17, and 33 of 48; four passes (B 64, d 2048)
+// lose: 0.79 0.85 0.91.  Three passes only win over tiles of 32 samples, which
+// the staged sweep takes past d 1151.  At and below 2^16 rows passes lose,
+// or are even (B 17 at 2^13 rows, d 128: 34.1 against 34.7 us).
+inline bool wide_takes(int64_t L, int32_t d, int32_t B) {
+    const int64_t size = L * d;
+    return B <= WD_PASS_B || (B <= 2 * WD_PASS_B && size >= ((int64_t)1 << 30)) ||
+           (B > 2 * WD_PASS_B && B <= WD_PASSES * WD_PASS_B && d > 1151 && size >= ((int64_t)1 << 29));
+}
+// layers of up to B_max samples some of whose batches take several passes
+inline bool wide_carries(int64_t L, int32_t d, int32_t B_max) {
+    return B_max > WD_PASS_B && (wide_takes(L, d, 2 * WD_PASS_B) || (B_max > 2 * WD_PASS_B && wide_takes(L, d, WD_PASSES * WD_PASS_B)));
 }
 // layers whose shape the fan-in-32 fast path serves (bf16 values)
 inline bool mx_shape(int64_t L, int32_t d, int32_t k) {
@@ -159,7 +179,7 @@ struct FastBufs {
 bool sweep_mx_eligible(const Layer &ly, int B, int mode);
 int launch_sweep_mx(const SweepCall &c, const FastBufs &fb, int *grid_out, int *passes_out);
 bool sweep_wide_eligible(const Layer &ly, int B, int mode);
-int launch_sweep_wide(const SweepCall &c, const FastBufs &fb, int *grid_out);
+int launch_sweep_wide(const SweepCall &c, const FastBufs &fb, int *grid_out, int *passes_out);
 int launch_adam(const Layer &ly, const AdamParams &p, hipStream_t st);
 // SET; in threshold mode (tau >= 0) every slot with |W| < tau is pruned and n
 // is ignored

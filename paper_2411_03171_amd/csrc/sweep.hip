@@ -607,10 +607,10 @@ int launch_sweep(const SweepCall &c) {
     int grid = (int)std::min<int64_t>(a.nchunks, ly.max_parts);
 
     // the fused fast paths.  Fan-in 64: one pass of 16 samples (1048576 rows, d
-    // 2048, B 16: 479 us against 1032 staged; two passes and more lose, B 64 at
-    // d 768: 1514 against 912).  Fan-in 32: one pass of 64, or several over many
-    // rows (MX_PASSES_MIN_L).
-    const bool use_wide = wl.has_xt && sweep_wide_eligible(ly, B, c.mode);
+    // 2048, B 16: 479 us against 1032 staged), two or three in the largest layers
+    // (wide_takes).  Fan-in 32: one pass of 64, or several over many rows
+    // (MX_PASSES_MIN_L).
+    const bool use_wide = wl.has_xt && sweep_wide_eligible(ly, B, c.mode) && (B <= WD_PASS_B || wl.has_partial);
     const bool use_mx =
         !use_wide && wl.has_xt && sweep_mx_eligible(ly, B, c.mode) && (B <= MX_PASS_B || wl.has_partial);
     const bool fast = use_wide || use_mx;
@@ -644,7 +644,7 @@ int launch_sweep(const SweepCall &c) {
                                    c.stream);
         if (rc) return rc;
         int passes = 1;
-        rc = use_wide ? launch_sweep_wide(c, fb, &grid) : launch_sweep_mx(c, fb, &grid, &passes);
+        rc = use_wide ? launch_sweep_wide(c, fb, &grid, &passes) : launch_sweep_mx(c, fb, &grid, &passes);
         if (rc) return rc;
         return finish_sweep(c, a.loss_part, a.dx_part, grid * passes, B, d, grid);
     }

@@ -5,23 +5,23 @@
 // At d = 2048 neither X for 64 samples (256 KB) nor a 32-row weight tile for
 // the dX product (128 KB) fits next to the other in the 160 KB of LDS, and a
 // dX accumulator of 64 samples (512 KB) exceeds the register file; 16 samples
-// fit.  This path takes batches of up to 16 in one sweep over the [L,k] arrays
-// (1048576 rows, d 2048: 479 us; the staged sweep takes 1032, and wins from 17
-// samples on, where this one would need a second pass):
+// fit.  This path takes batches of up to 16 in one sweep over the [L,k] arrays,
+// and of up to 48 in passes of 16 (see launch_sweep_wide) where those are
+// faster than the staged sweep (wide_takes):
 //
 // Workgroup: 512 threads (8 waves), one per CU, persistent over chunks of 16
 // label rows.  Thirty-two lanes serve one row: lane u handles the four
-// samples 4q .. 4q+3, q = u >> 3, and the eight slots
+// samples 4q .. 4q+3 of the pass, q = u >> 3, and the eight slots
 // 8g .. 8g+7 of the row, g = u & 7.
 //
-//   LDS  Xs [d][16] bf16   the batch transposed (column i is 32 contiguous
-//                          bytes), zero-padded past B
+//   LDS  Xs [d][16] bf16   the pass's samples transposed (column i is 32
+//                          contiguous bytes), zero-padded past the pass
 //        T  [d][16] bf16   the chunk's weights scattered densely by column
 //        G  [16][16] bf16  the chunk's dlogits (both with the 8-byte quarters
 //                          of a row rotated every 4 rows, see qswz)
 //        Is, Ws            the chunk's index rows (as byte offsets into Xs)
 //                          and weight rows; each wave stages its own two rows
-//        tg                the positives as sorted (label, sample) keys
+//        tg                the pass's positives as sorted (label, sample) keys
 //
 //   1. gather: for each of its 8 slots the lane reads the 8 bytes
 //      X[4q .. 4q+3, I[l,j]]; the sample pairs are repacked into slot pairs
@@ -52,7 +52,7 @@ using namespace fdev;
 constexpr int WD_THREADS = 512;
 constexpr int WD_NLAB = 16;      // label rows per chunk
 constexpr int WD_K = 64;         // fan-in of this path
-constexpr int WD_NB = 16;        // samples at most
+constexpr int WD_NB = 16;        // samples per pass
 constexpr int WD_XS = 32;        // bytes per X column row in LDS
 constexpr int WD_TG_MAX = 1024;  // positives kept in LDS
 constexpr int WD_NT_MAX = 16;    // widest input: 2048 columns
@@ -77,11 +77,15 @@ struct WdArgs {
     // that the chunk loop uses for an access that must not happen
     uint32_t nb_W, nb_I, nb_m, nb_b;
     int32_t idx16;   // I holds uint16 indices
+    // batch pass: samples b0 .. b0+B-1 of Btot; dW / dbias carried between
+    // passes in dwp [L][64], dbp [L]
+    int32_t b0, Btot;
+    float *dwp, *dbp;
     int32_t hinge;   // squared hinge instead of BCE
 };
 
 struct Rsrcs {
-    Rsrc XT, K, W, I, m, v, b, bm, bv;
+    Rsrc XT, K, W, I, m, v, b, bm, bv, dwp, dbp;
 };
 
 // G and T rows hold 16 bf16 (32 bytes = four 8-byte quarters).  A matrix-core
@@ -99,9 +103,11 @@ struct Prefetch {
     float b;           // its bias
 };
 
-// the chunk's rows and optimiser state, loaded a chunk ahead of their use; a
-// chunk or row past the end reads zeros.  Lane tid loads words of row tid / 32 only: a row its wave
+// the chunk's rows and optimiser state (the moments only for a pass that
+// applies Adam), loaded a chunk ahead of their use; a chunk or row past the
+// end reads zeros.  Lane tid loads words of row tid / 32 only: a row its wave
 // serves.
+template <bool MOMENTS>
 __device__ __forceinline__ void prefetch(const WdArgs &a, const Rsrcs &R, int64_t chunk, int tid, int lab,
                                          int slot, Prefetch &p) {
     const int64_t l0 = chunk * WD_NLAB;
@@ -116,14 +122,20 @@ __device__ __forceinline__ void prefetch(const WdArgs &a, const Rsrcs &R, int64_
     const int64_t l = l0 + lab;
     const bool ok = live && l < a.L;
     const uint32_t om = ok ? (uint32_t)(l * WD_K + slot) * 4u : a.nb_m;
-    p.m = ldf2(R.m, om);
-    p.v = ldf2(R.v, om);
+    if constexpr (MOMENTS) {
+        p.m = ldf2(R.m, om);
+        p.v = ldf2(R.v, om);
+    } else {
+        p.m = p.v = make_float2(0.f, 0.f);
+    }
     p.b = ldf(R.b, ok ? (uint32_t)l * 4u : a.nb_b);
 }
 
 // NT = d / 128: the d / 16 column tiles of 16 are dealt to the 8 waves, NT each
-template <int NT>
+template <int NT, int MODE>
 __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
+    constexpr bool ADAM = MODE == PASS_ONLY || MODE == PASS_LAST;      // updates W, m, v, bias
+    constexpr bool CARRY_IN = MODE == PASS_LAST || MODE == PASS_MIDDLE;
     constexpr int d = 128 * NT;
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned char *Xs = lds;                                                  // d * 32
@@ -155,9 +167,11 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
     R.b = make_rsrc(a.bias, a.nb_b);
     R.bm = make_rsrc(a.bm, a.nb_b);
     R.bv = make_rsrc(a.bv, a.nb_b);
+    R.dwp = make_rsrc(a.dwp, MODE == PASS_ONLY ? 0u : a.nb_m);
+    R.dbp = make_rsrc(a.dbp, MODE == PASS_ONLY ? 0u : a.nb_b);
 
     Prefetch pa, pb;
-    prefetch(a, R, blockIdx.x, tid, lab, myslot, pa);
+    prefetch<ADAM>(a, R, blockIdx.x, tid, lab, myslot, pa);
 
     // stage the pass's X tile (transposed and zero-padded past B by the batch
     // prep) with 16-byte copies, its sorted positives, and clear T and G.  The
@@ -208,7 +222,7 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
             *reinterpret_cast<int2 *>(Is + 2 * tid) = make_int2(i0 * WD_XS, i1 * WD_XS);
             reinterpret_cast<uint32_t *>(Ws)[tid] = cur.wv;
         }
-        prefetch(a, R, chunk + gridDim.x, tid, lab, myslot, nxt);
+        prefetch<ADAM>(a, R, chunk + gridDim.x, tid, lab, myslot, nxt);
 
         // targets of this lane's row as a 16-bit sample mask
         uint32_t yrow = 0;
@@ -233,7 +247,7 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
             const uint32_t r0 = l0u + 2u * (uint32_t)wave;
             for (int e = lane; e < nnz; e += 64) {
                 const uint32_t ll = (uint32_t)a.tgt_lab[e] - r0;
-                const uint32_t b = (uint32_t)a.tgt_b[e];
+                const uint32_t b = (uint32_t)(a.tgt_b[e] - a.b0);
                 if (ll < 2u && b < (uint32_t)a.B) atomicOr(&ymw[ll], 1u << b);
             }
             wave_lds_sync();
@@ -247,7 +261,18 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
         const int64_t l = l0 + rl;
         const bool valid = l < a.L;
         const uint32_t obm = valid && u == 0 ? (uint32_t)l * 4u : a.nb_b;
-        const float bmcur = ldf(R.bm, obm), bvcur = ldf(R.bv, obm);
+        float bmcur = 0.f, bvcur = 0.f;
+        if constexpr (ADAM) {
+            bmcur = ldf(R.bm, obm);
+            bvcur = ldf(R.bv, obm);
+        }
+        const uint32_t odw = valid ? (uint32_t)(l * WD_K + myslot) * 4u : a.nb_m;
+        float2 dprev = make_float2(0.f, 0.f);
+        float dbprev = 0.f;
+        if constexpr (CARRY_IN) {
+            dprev = ldf2(R.dwp, odw);
+            dbprev = ldf(R.dbp, obm);
+        }
 
         // gather the lane's 8 slots for its 4 samples: registers 2p, 2p+1
         // hold slots 2(p ^ kq), 2(p ^ kq) + 1 of the group, each as the
@@ -319,7 +344,7 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
         const uint32_t g01 = pack_bf16(g[0], g[1]), g23 = pack_bf16(g[2], g[3]);
         // a wave whose dlogits are all zero (a hinge loss past its margin
         // everywhere, Sec. 2.2) has zero dW: its products are skipped
-        float dw0 = 0.f, dw1 = 0.f;
+        float dw0 = dprev.x, dw1 = dprev.y;
         if (__builtin_amdgcn_ballot_w64((g01 | g23) != 0u) != 0) {
             float pw[8];
 #pragma unroll
@@ -333,7 +358,8 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
             dw0 += add_dpp<DPP_ROW_ROR8>(r4[0], r4[2]);
             dw1 += add_dpp<DPP_ROW_ROR8>(r4[1], r4[3]);
         }
-        {
+        if constexpr (!ADAM) stf2(R.dwp, odw, make_float2(dw0, dw1));
+        if constexpr (ADAM) {
             float m0 = cur.m.x, m1 = cur.m.y, v0 = cur.v.x, v1 = cur.v.y;
             const float w0 = __uint_as_float(wown << 16);
             const float w1 = __uint_as_float(wown & 0xffff0000u);
@@ -349,13 +375,15 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
         {
             float sg = (g[0] + g[1]) + (g[2] + g[3]);
             sg = cross_rows_add(sg, sg);
-            sg = add_dpp<DPP_ROW_ROR8>(sg, sg);
-            {
+            sg = add_dpp<DPP_ROW_ROR8>(sg, sg) + dbprev;
+            if constexpr (ADAM) {
                 float mm = bmcur, vv = bvcur;
                 const float nb = adam_step(cur.b, sg, mm, vv, b1, b2, inv_bc1, inv_bc2, lr, eps, decay);
                 stf(R.b, obm, nb);
                 stf(R.bm, obm, mm);
                 stf(R.bv, obm, vv);
+            } else {
+                stf(R.dbp, obm, sg);
             }
         }
         // Every wave has read the previous chunk's G and T fragments before
@@ -394,9 +422,9 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
         step(chunk + gridDim.x, pb, pa);
     }
 
-    // write this workgroup's dX partial [B][d]
+    // write this workgroup's dX partial [B][d] (its rows of the pass)
     {
-        float *P = a.dx_part + (size_t)blockIdx.x * a.B * d;
+        float *P = a.dx_part + ((size_t)blockIdx.x * a.Btot + a.b0) * d;
         const int col = lane & 15, kq = lane >> 4;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -421,13 +449,18 @@ __global__ void __launch_bounds__(WD_THREADS, 1) k_sweep_wide(const WdArgs a) {
 }
 
 typedef void (*WdKernel)(const WdArgs);
+template <int NT>
+struct WdModes {
+    static constexpr WdKernel k[4] = {k_sweep_wide<NT, PASS_ONLY>, k_sweep_wide<NT, PASS_FIRST>,
+                                      k_sweep_wide<NT, PASS_LAST>, k_sweep_wide<NT, PASS_MIDDLE>};
+};
 template <int... NTs>
-WdKernel wd_pick(int nt, std::integer_sequence<int, NTs...>) {
+WdKernel wd_pick(int nt, int mode, std::integer_sequence<int, NTs...>) {
     WdKernel r = nullptr;
-    ((nt == NTs + 1 ? (r = k_sweep_wide<NTs + 1>, 0) : 0), ...);
+    ((nt == NTs + 1 ? (r = WdModes<NTs + 1>::k[mode], 0) : 0), ...);
     return r;
 }
-WdKernel wd_kernel(int nt) { return wd_pick(nt, std::make_integer_sequence<int, WD_NT_MAX>{}); }
+WdKernel wd_kernel(int nt, int mode) { return wd_pick(nt, mode, std::make_integer_sequence<int, WD_NT_MAX>{}); }
 
 size_t sweep_wide_lds(int d) {
     return (size_t)d * WD_XS + (size_t)d * WD_NLAB * 2 + WD_NB * WD_NLAB * 2 + WD_NLAB * WD_K * 4 +
@@ -438,11 +471,16 @@ size_t sweep_wide_lds(int d) {
 
 bool sweep_wide_eligible(const Layer &ly, int B, int mode) {
     static_assert(WD_NB == WD_PASS_B, "pass width");
-    return mode == SWEEP_FUSED && B <= WD_NB && ly.vt == FFSL_BF16 && wide_shape(ly.L, ly.d, ly.k) && ly.k == WD_K &&
+    return mode == SWEEP_FUSED && wide_takes(ly.L, ly.d, B) && ly.vt == FFSL_BF16 && wide_shape(ly.L, ly.d, ly.k) && ly.k == WD_K &&
            ly.d <= 128 * WD_NT_MAX && sweep_wide_lds(ly.d) <= 160 * 1024;
 }
 
-int launch_sweep_wide(const SweepCall &c, const FastBufs &fb, int *grid_out) {
+// The batch runs in passes of 16 samples: every pass accumulates its samples'
+// dX rows and loss, the first stores its dW / dbias in the carry buffers,
+// middle passes add to them, and the last adds its share and applies Adam.
+// W, the moments and the bias change only in the last pass, so every pass
+// sees the step's old state.
+int launch_sweep_wide(const SweepCall &c, const FastBufs &fb, int *grid_out, int *passes_out) {
     const Layer &ly = *c.layer;
     WdArgs a{};
     a.L = ly.L;
@@ -461,10 +499,9 @@ int launch_sweep_wide(const SweepCall &c, const FastBufs &fb, int *grid_out) {
     a.s = c.s;
     a.adam = c.adam;
     a.dx_part = fb.dx_part;
-    a.B = c.B;
-    a.XT = fb.xt;
-    a.keys = fb.keys;
-    a.loss_part = fb.loss_part;
+    a.dwp = fb.dwp;
+    a.dbp = fb.dbp;
+    a.Btot = c.B;
     a.hinge = (c.flags & FFSL_LOSS_SQHINGE) ? 1 : 0;
     a.nb_W = (uint32_t)(ly.L * WD_K * 2);
     a.idx16 = ly.idx16;
@@ -473,22 +510,32 @@ int launch_sweep_wide(const SweepCall &c, const FastBufs &fb, int *grid_out) {
     a.nb_b = ly.bias ? (uint32_t)(ly.L * 4) : 0u;
     const size_t shm = sweep_wide_lds(ly.d);
     const int grid = (int)std::min<int64_t>(a.nchunks, std::min(ly.max_parts, ly.num_cu));
+    const int passes = (c.B + WD_NB - 1) / WD_NB;
     if (ly.ev_start) {
         hipError_t e = hipEventRecord(ly.ev_start, c.stream);
         if (e != hipSuccess) return fail(FFSL_EHIP, "hipEventRecord: %s", hipGetErrorString(e));
     }
-    const WdKernel kern = wd_kernel(ly.d / 128);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
-    if (e != hipSuccess) return fail(FFSL_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(WD_THREADS), shm, c.stream, a);
-    int rc = check_launch("sweep_wide");
-    if (rc) return rc;
+    for (int p = 0; p < passes; ++p) {
+        const int mode = passes == 1 ? PASS_ONLY : p == 0 ? PASS_FIRST : p == passes - 1 ? PASS_LAST : PASS_MIDDLE;
+        a.b0 = p * WD_NB;
+        a.B = std::min(WD_NB, c.B - a.b0);
+        a.XT = fb.xt + (size_t)p * ly.d * WD_NB;
+        a.keys = fb.keys + (size_t)p * WD_TG_MAX;
+        a.loss_part = fb.loss_part + (size_t)p * grid;
+        const WdKernel kern = wd_kernel(ly.d / 128, mode);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+        if (e != hipSuccess) return fail(FFSL_EHIP, "hipFuncSetAttribute: %s", hipGetErrorString(e));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(WD_THREADS), shm, c.stream, a);
+        int rc = check_launch("sweep_wide");
+        if (rc) return rc;
+    }
     if (ly.ev_stop) {
-        e = hipEventRecord(ly.ev_stop, c.stream);
+        hipError_t e = hipEventRecord(ly.ev_stop, c.stream);
         if (e != hipSuccess) return fail(FFSL_EHIP, "hipEventRecord: %s", hipGetErrorString(e));
     }
     *grid_out = grid;
+    *passes_out = passes;
     return FFSL_OK;
 }
 
