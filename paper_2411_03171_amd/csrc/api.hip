@@ -64,8 +64,6 @@ WsLayout ws_layout(int64_t L, int32_t d, int32_t k, int32_t vt, int32_t B_max, i
     off = align256(off + sizeof(float) * (size_t)max_parts * (size_t)((B_max + 15) / 16));
     w.tgt_b = off;
     off = align256(off + sizeof(int32_t) * (size_t)std::max(nnz_max, 1));
-    w.dx_part = off;
-    off = align256(off + sizeof(float) * (size_t)max_parts * (size_t)B_max * (size_t)d);
     w.has_partial = wide_carry || (mx && B_max > MX_PASS_B && L >= MX_PASSES_MIN_L);
     w.dwp = off;
     if (w.has_partial) off = align256(off + sizeof(float) * (size_t)L * (size_t)k);
@@ -86,11 +84,22 @@ WsLayout ws_layout(int64_t L, int32_t d, int32_t k, int32_t vt, int32_t B_max, i
     if (w.has_staged) off = align256(off + staged_xb_bytes(d, vt, B_max));
     w.st_pos = off;
     if (w.has_staged) off = align256(off + sizeof(int2) * (size_t)std::max(nnz_max, 1));
-    w.st_g = off;
-    w.st_g_bytes = w.has_staged ? staged_g_bytes(L, B_max) : 0;
-    off = align256(off + w.st_g_bytes);
-    w.st_gsum = off;
-    if (w.has_staged) off = align256(off + staged_gsum_bytes(L, B_max));
+    // The dX partials come last: G takes what the staged sweep leaves of them and
+    // goes on past their end, or as far as the caller's workspace does.  Layers
+    // whose fused steps all take a fast path need G for separate calls only, and
+    // ask for no more than what is left of the partials.
+    const size_t dx_one = sizeof(float) * (size_t)B_max * (size_t)d;
+    const size_t dx_all = dx_one * (size_t)max_parts, dx_used = align256(dx_one * (size_t)staged_max_parts(max_parts));
+    if (w.has_staged) {
+        const bool fused_fast = (wide && B_max <= WD_PASS_B) || (mx && (B_max <= MX_PASS_B || w.has_partial));
+        w.st_g_bytes = staged_g_bytes(L, B_max);
+        w.st_gsum = off;
+        off = align256(off + staged_gsum_bytes(L, B_max, fused_fast ? 3 : 1));
+        if (fused_fast) w.st_g_bytes = std::max(std::min(w.st_g_bytes, dx_all - std::min(dx_all, dx_used)), staged_g_bytes(1, B_max));
+    }
+    w.dx_part = off;
+    w.st_g = off + dx_used;
+    off = align256(off + std::max(dx_all, w.has_staged ? dx_used + w.st_g_bytes : 0));
     w.total = off;
     return w;
 }

@@ -41,7 +41,8 @@ struct WsLayout {
     bool has_xt;        // the shape may take a fused fast path (keys, xt allocated)
     size_t st_xa, st_xb;      // the staged sweep's X images (staged.h)
     size_t st_pos;            // its positives, int2 [nnz_max]
-    size_t st_g, st_g_bytes;  // its loss gradients of a slab of rows
+    size_t st_g, st_g_bytes;  // its loss gradients of a slab of rows (may share
+                              // the dX partials that it does not use)
     size_t st_gsum;           // their sums over samples
     bool has_staged;
     size_t total;

@@ -431,9 +431,10 @@ size_t staged_g_bytes(int64_t L, int32_t B_max) {
     return al256((size_t)std::min<int64_t>(rows, std::max<int64_t>((STAGED_G_MAX + per_row - 1) / per_row, 64)) * (size_t)per_row);
 }
 
-// a sum per (tile, row) of G, whose tiles hold 16 samples and one plane at least
-size_t staged_gsum_bytes(int64_t L, int32_t B_max) {
-    return al256((size_t)std::min<int64_t>((L + 63) / 64 * 64 * ((B_max + 15) / 16), (int64_t)(staged_g_bytes(L, B_max) / 32)) * 4);
+// a sum per (tile, row) of G, whose tiles hold 16 samples and min_S planes at
+// least
+size_t staged_gsum_bytes(int64_t L, int32_t B_max, int min_S) {
+    return al256((size_t)std::min<int64_t>((L + 63) / 64 * 64 * ((B_max + 15) / 16), (int64_t)(staged_g_bytes(L, B_max) / (32 * min_S))) * 4);
 }
 
 StagedPlan staged_plan(const Layer &ly, int B, int S, size_t g_bytes) {

@@ -447,7 +447,8 @@ static int launch_staged(const SweepCall &c, const WsLayout &wl) {
     // the fused step of the bf16 shapes that have a fast path rounds g to bf16
     // for the products, as that path does; elsewhere g keeps its 24 bits
     const bool one = c.mode == SWEEP_FUSED && bf && (wide_shape(ly.L, ly.d, ly.k) || mx_shape(ly.L, ly.d, ly.k));
-    const StagedPlan p = staged_plan(ly, c.B, c.mode == SWEEP_FWD ? 0 : one ? 1 : 3, wl.st_g_bytes);
+    const size_t g_bytes = std::min(staged_g_bytes(ly.L, ly.B_max), ly.ws_bytes - wl.st_g);
+    const StagedPlan p = staged_plan(ly, c.B, c.mode == SWEEP_FWD ? 0 : one ? 1 : 3, g_bytes);
     float *loss_part = reinterpret_cast<float *>(ly.ws + wl.loss_part);
     float *dx_part = reinterpret_cast<float *>(ly.ws + wl.dx_part);
     uint16_t *G = p.S ? reinterpret_cast<uint16_t *>(ly.ws + wl.st_g) : nullptr;
