@@ -461,7 +461,11 @@ StagedPlan staged_plan(const Layer &ly, int B, int S, size_t g_bytes) {
     // their image again (about 52 us of a step of 1048576 rows, fan-in 64, d 2048,
     // B 128, whose third slab had 128 rows)
     const int64_t slabs = (ly.L + most_rows - 1) / most_rows;
-    p.slab = ((ly.L + slabs - 1) / slabs + 63) / 64 * 64;
+    const int64_t even = (ly.L + slabs - 1) / slabs;
+    // whole steps of 16 waves on every CU where that leaves as many slabs: the
+    // last step of seven slabs of 149797 rows was a ninth full
+    const int64_t unit = (int64_t)ly.num_cu * 64, whole = (even + unit - 1) / unit * unit;
+    p.slab = slabs > 1 && whole <= most_rows ? whole : (even + 63) / 64 * 64;
     return p;
 }
 
