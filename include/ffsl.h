@@ -99,11 +99,11 @@ FFSL_API int ffsl_version(void);
  * The other fused steps and the unfused calls keep two images of the batch (up
  * to 12 bytes per input) and the loss gradients of a slab of rows (6 bytes per
  * sample and row, 128 MiB at most and partly in room the partial sums leave,
- * and 4 bytes per 16 samples and row, 16 MiB at most).  A layer whose fused
- * steps need none of the latter asks for the room the partial sums leave only;
- * its unfused calls then take more slabs, and fewer (16% less time at 3 million
- * rows) if its workspace is larger by those 6 bytes per sample and row, up to
- * 128 MiB.
+ * and 4 bytes per 16 samples and row, 16 MiB at most).  A layer of a fused fast
+ * path and one pass (B_max <= 64 at fan-in 32, <= 16 at fan-in 64) asks for the
+ * room the partial sums leave only: its unfused calls take more slabs then, and
+ * fewer (18% less time at 3 million rows) if its workspace is larger by those 6
+ * bytes per sample and row, up to 128 MiB.
  * Returns 0 for invalid shapes. */
 FFSL_API size_t ffsl_workspace_bytes(int64_t L, int32_t d, int32_t k, int32_t B_max,
                             int32_t nnz_max);

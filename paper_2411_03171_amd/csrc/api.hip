@@ -86,12 +86,13 @@ WsLayout ws_layout(int64_t L, int32_t d, int32_t k, int32_t vt, int32_t B_max, i
     if (w.has_staged) off = align256(off + sizeof(int2) * (size_t)std::max(nnz_max, 1));
     // The dX partials come last: G takes what the staged sweep leaves of them and
     // goes on past their end, or as far as the caller's workspace does.  Layers
-    // whose fused steps all take a fast path need G for separate calls only, and
-    // ask for no more than what is left of the partials.
+    // whose fused steps all take one pass of a fast path need G for separate calls
+    // only, and ask for no more than what is left of the partials (those of
+    // several passes carry dW in memory anyway).
     const size_t dx_one = sizeof(float) * (size_t)B_max * (size_t)d;
     const size_t dx_all = dx_one * (size_t)max_parts, dx_used = align256(dx_one * (size_t)staged_max_parts(max_parts));
     if (w.has_staged) {
-        const bool fused_fast = (wide && B_max <= WD_PASS_B) || (mx && (B_max <= MX_PASS_B || w.has_partial));
+        const bool fused_fast = (wide && B_max <= WD_PASS_B) || (mx && B_max <= MX_PASS_B);
         w.st_g_bytes = staged_g_bytes(L, B_max);
         w.st_gsum = off;
         off = align256(off + staged_gsum_bytes(L, B_max, fused_fast ? 3 : 1));

@@ -158,8 +158,7 @@ class SparseLayer:
         nbytes = lib.ffsl_workspace_bytes_ex(self.L, self.d, self.k, self.vt, self.B_max, self.nnz_max)
         if nbytes == 0:
             raise FfslError(FFSL_EINVAL, lib.ffsl_last_error().decode())
-        fast = self.B_max <= 16 if self.k == 64 else self.k == 32 and (self.B_max <= 64 or self.L > 1 << 18)
-        if self.dW is not None and self.vt == FFSL_BF16 and self.d % 128 == 0 and fast:
+        if self.dW is not None and self.vt == FFSL_BF16 and self.d % 128 == 0 and self.B_max <= {32: 64, 64: 16}.get(self.k, 0):
             # room for the unfused calls of a layer whose fused steps need none
             nbytes += min(128 << 20, 6 * (self.B_max + 63) * self.L)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.W.device)

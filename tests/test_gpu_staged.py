@@ -414,3 +414,36 @@ def test_fused_step_over_several_slabs(torch_cuda, case):
     assert_close(layer.bias.cpu().numpy(), bn, RTOL_F32, "bias")
     Wg = values_f64(from_torch_bits(layer.W, w.value), w.value)
     assert_close(Wg, Wn, RTOL_F32 if w.value == "f32" else 2.0 ** -8, "W")   # bf16: half an ulp
+
+
+def test_unfused_calls_in_the_least_and_in_a_larger_workspace(torch_cuda):
+    """A fan-in-32 layer of one pass: its typed workspace cuts a backward call of
+    50000 rows into three slabs, the binding's larger one into one.  Same
+    gradients bit for bit, dX up to the order of its sums."""
+    import ctypes
+    torch = torch_cuda
+    from paper_2411_03171_amd import ffsl
+    w = shape("bf16", 50000, 128, 32, 64)
+    inp, bias = inputs(w, 14)
+    X, off, lab = batch_to_gpu(inp.X, inp.off, inp.lab, w.value)
+    layer = make_gpu_layer(inp, w, bias_values=bias)
+    lib = ffsl.load()
+    least = lib.ffsl_workspace_bytes_ex(w.L, w.d, w.k, ffsl.FFSL_BF16, w.B, layer.nnz_max)
+    assert layer.workspace.numel() >= least + (16 << 20)
+    note("staged in a larger workspace")
+    dX = layer.backward(X, off, lab)
+    dW, db = layer.dW.clone(), layer.dbias.clone()
+    layer.close()
+    ptr = ffsl._ptr
+    h = ctypes.c_void_p()
+    ffsl._check(lib.ffsl_create_layer_ex(ctypes.byref(h), w.L, w.d, w.k, ffsl.FFSL_BF16, layer.idx, ptr(layer.W), ptr(layer.I),
+                                         ptr(layer.bias), ptr(layer.m), ptr(layer.v), ptr(layer.bias_m), ptr(layer.bias_v),
+                                         ptr(layer.dW), ptr(layer.dbias), ptr(layer.workspace), least, w.B, layer.nnz_max))
+    layer._handle = h
+    tail = layer.workspace[least:].fill_(7)
+    layer.dW.fill_(np.nan)
+    note("staged in the least workspace")
+    dX2 = layer.backward(X, off, lab)
+    assert torch.equal(layer.dW, dW) and torch.equal(layer.dbias, db)
+    assert_close(dX2.cpu().numpy(), dX.cpu().numpy(), RTOL_F32, "dX")
+    assert bool((tail == 7).all())
