@@ -402,6 +402,8 @@ template <int VT, int NP, int S>
 ScoreKernel score_s(bool full, bool idx16) {
     if constexpr (VT == FFSL_F32)
         return k_score<VT, NP, S, false, false>;
+    else if constexpr (S == 1)   // fan-in 32 and 64 only
+        return idx16 ? k_score<VT, NP, S, true, true> : k_score<VT, NP, S, true, false>;
     else
         return full ? (idx16 ? k_score<VT, NP, S, true, true> : k_score<VT, NP, S, true, false>)
                     : (idx16 ? k_score<VT, NP, S, false, true> : k_score<VT, NP, S, false, false>);
@@ -409,7 +411,9 @@ ScoreKernel score_s(bool full, bool idx16) {
 template <int VT, int NP>
 ScoreKernel score_np(int S, bool full, bool idx16) {
     if (S == 0) return score_s<VT, NP, 0>(full, idx16);
-    if constexpr (VT == FFSL_BF16)
+    // one plane: batches that a fused fast path does not take, of 17 samples at
+    // least
+    if constexpr (VT == FFSL_BF16 && NP >= 2)
         if (S == 1) return score_s<VT, NP, 1>(full, idx16);
     return score_s<VT, NP, 3>(full, idx16);
 }

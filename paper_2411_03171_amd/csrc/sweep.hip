@@ -449,6 +449,8 @@ static int launch_staged(const SweepCall &c, const WsLayout &wl) {
     const bool one = c.mode == SWEEP_FUSED && bf && (wide_shape(ly.L, ly.d, ly.k) || mx_shape(ly.L, ly.d, ly.k));
     const size_t g_bytes = std::min(staged_g_bytes(ly.L, ly.B_max), ly.ws_bytes - wl.st_g);
     const StagedPlan p = staged_plan(ly, c.B, c.mode == SWEEP_FWD ? 0 : one ? 1 : 3, g_bytes);
+    if (p.S == 1 && p.BT < 32)
+        return fail(FFSL_EUNSUPPORTED, "staged sweep: one plane of g is built for tiles of 32 samples and more");
     float *loss_part = reinterpret_cast<float *>(ly.ws + wl.loss_part);
     float *dx_part = reinterpret_cast<float *>(ly.ws + wl.dx_part);
     uint16_t *G = p.S ? reinterpret_cast<uint16_t *>(ly.ws + wl.st_g) : nullptr;
