@@ -1,10 +1,11 @@
-"""Targets on the fused fast paths, whose positives are sorted once per call
-into per-pass key lists: no positives, a sample without positives, repeated
-labels, labels outside [0,L) (ignored, as the header states), and positive
-counts at and just past the 1024 the sweeps keep on chip (beyond it they scan
-the CSR arrays).  Loss, dX and dW (read from the first Adam moment,
-m = (1 - beta1) dW when it starts at zero) are checked against the oracle run
-on the in-range labels."""
+"""Targets of the fused step: of the fused fan-in-32 path, whose positives are
+sorted once per call into key lists (past 1024 of them it scans the CSR arrays),
+and of the staged sweep, which keeps them as bits (those of the fused fan-in-64
+path: test_gpu_wide).  No positives, a sample without positives, repeated
+labels, labels outside [0,L) (ignored, as the header states), and 1024 and 1025
+positives.  Loss, dX and dW (read from the first Adam moment, m = (1 - beta1) dW
+when it starts at zero) are checked against the oracle run on the in-range
+labels."""
 import numpy as np
 import pytest
 
@@ -17,9 +18,11 @@ pytestmark = pytest.mark.gpu
 W1 = synth.WORKLOADS
 
 SHAPES = {
-    # fan-in 32 at d = 768: two batch passes of 64 samples
+    # the fused fan-in-32 path: one pass of 64 samples, ragged
+    "mx60": synth.scaled(W1["c4_bf16_L3M"], L=700, B=60, name="mx_targets"),
+    # fan-in 32 at d = 768, B = 100: two tiles of the staged sweep
     "mx": synth.scaled(W1["c4_bf16_L3M"], L=700, B=100, name="mx_targets"),
-    # fan-in 64 on the wide path: three passes of 16 samples, the last ragged
+    # fan-in 64, B = 40: one tile of the staged sweep, ragged
     "wide": synth.dataclasses.replace(synth.scaled(W1["c3_inter2048_L1M"], L=500, d=256, B=40,
                                                    name="wide_targets"), din=0),
 }

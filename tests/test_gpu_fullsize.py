@@ -6,7 +6,8 @@ fused training step (ffsl_train_step) on a freshly created layer.
   the loss and dX sum over blocks), so every row's W, m, v and bias is
   checked, as are the loss and the full dX.
 - The C3 and C5 sparse layers (L = 1 048 576, B = 128; fan-in 64 at width
-  2048, fan-in 32 at width 768), whose steps run in several batch passes:
+  2048: the staged sweep over two slabs and four tiles; fan-in 32 at width 768:
+  two batch passes):
   sampled outputs the oracle computes cheaply, three row blocks' state over
   every sample and four samples' dX over every row."""
 import numpy as np
@@ -106,8 +107,8 @@ def test_fused_step_full_c4():
 
 
 SAMPLED = {
-    # the C3 sparse layer (fan-in 64, width 2048: eight 16-sample passes) and
-    # the C5 sparse layer (fan-in 32, width 768: two 64-sample passes)
+    # the C3 sparse layer (fan-in 64, width 2048: the staged sweep) and the C5
+    # sparse layer (fan-in 32, width 768: two 64-sample passes)
     "c3": synth.dataclasses.replace(synth.WORKLOADS["c3_inter2048_L1M"], din=0),
     "c5": synth.dataclasses.replace(synth.WORKLOADS["c5_aux8192_L1M"], aux_clusters=0),
 }
@@ -118,7 +119,7 @@ SAMPLES = [0, 37, 90, 127]
 @pytest.mark.parametrize("name", list(SAMPLED))
 def test_fused_step_full_sampled(name):
     """The full C3 and C5 sparse layers in the launch configuration the
-    benchmark times (all batch passes of one fused step): W, m, v and bias of
+    benchmark times (all passes or slabs of one fused step): W, m, v and bias of
     three 32768-row blocks against the oracle over those rows and every
     sample, and four samples' dX rows against the oracle over every row."""
     import torch

@@ -5,9 +5,10 @@ SET (bit-exact on every row), and its top-k inference.  Against the same
 layer with int32 indices: every call must give the same results -- the
 storage differs, the arithmetic does not.  Compared bit for bit
 (weights, indices, moments, bias, masks, loss, dX): every path forms its sums
-in a fixed order.  Shapes: the fan-in 32 fast path in one and several batch
-passes with and without fused SET, the wide fan-in 64 path, the general path
-(bf16 at width 320, fp32), SET in both prune modes, top-k inference."""
+in a fixed order.  Shapes: the fused fan-in-32 path in one pass
+with and without fused SET, the staged sweep (bf16 at fan-in 32 and 64, width
+320 and others, fp32), SET in both prune modes, top-k inference.  (Passes and
+the fused fan-in-64 path: test_gpu_wide.)"""
 import numpy as np
 import pytest
 

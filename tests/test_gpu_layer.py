@@ -30,15 +30,14 @@ CASES = {
     # count) with a ragged batch
     "mx128": synth.scaled(W1["c4_bf16_L3M"], L=257, d=128, B=64, name="mx128"),
     "mx320": synth.scaled(W1["c4_bf16_L3M"], L=1003, d=320, B=37, name="mx320"),
-    # a batch of 200 on the fused fast path: four passes (first, two middle, last)
+    # a batch of 200: four tiles of the staged sweep (passes: test_gpu_mx_passes)
     "mx200": synth.scaled(W1["c4_bf16_L3M"], L=777, B=200, name="mx200"),
     # more positives per batch (about 1900) than the fast path keeps on chip
     "mxdense": synth.dataclasses.replace(synth.scaled(W1["c4_bf16_L3M"], L=700, name="mxdense"),
                                          mean_pos=30.0),
-    # the fused bf16 fan-in-64 wide path (passes of 16 samples): another width
-    # with a ragged last pass and a ragged chunk, a single pass at the
-    # narrowest width, and more positives per pass (about 1300) than it keeps
-    # on chip
+    # fan-in 64: batches past 16 samples, which at these sizes take the staged
+    # sweep (one with about 10 thousand positives), and one pass of the fused
+    # path at its narrowest width (its other widths and passes: test_gpu_wide)
     "w1024": synth.scaled(W1["c3_inter2048_L1M"], L=777, d=1024, B=37, name="w1024"),
     "w128": synth.scaled(W1["c3_inter2048_L1M"], L=301, d=128, B=16, name="w128"),
     "wdense": synth.dataclasses.replace(synth.scaled(W1["c3_inter2048_L1M"], L=900, name="wdense"),

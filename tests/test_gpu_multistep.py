@@ -15,10 +15,10 @@ fan-in-32 fast path), the pre-SET state comes from a twin layer with the same
 state that runs the plain ffsl_train_step on the same batch.
 
 Cases: the largest workload's shape (B = 64, one batch pass of the fast path)
-and the LF-AmazonTitles-131K stand-in (B = 128, two batch passes), both with
-SET fused into the step; the fp32 correctness workload (general path, k = 16)
-and a bf16 width off the fast path (d = 320, general path), both with the step
-and SET as separate calls."""
+with SET fused into the step; the LF-AmazonTitles-131K stand-in (B = 128, two
+tiles of the staged sweep) through the same call, which there runs the two one
+after the other; the fp32 correctness workload (k = 16) and a bf16 width off
+the fast path (d = 320), both with the step and SET as separate calls."""
 import numpy as np
 import pytest
 
@@ -30,7 +30,7 @@ pytestmark = pytest.mark.gpu
 
 W1 = synth.WORKLOADS
 CASES = {
-    # name: (workload, SET fused into the step)
+    # name: (workload, step and SET in one call)
     "c4s": (synth.scaled(W1["c4_bf16_L3M"], L=3000, name="c4s"), True),
     "c2s": (synth.scaled(W1["c2_bf16_L131072"], L=3000, name="c2s"), True),
     "c1": (synth.scaled(W1["c1_fp32_L4096"], L=1500, name="c1m"), False),

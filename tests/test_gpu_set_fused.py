@@ -3,8 +3,8 @@ fused into the sweep that applies Adam.  Its contract is the result of
 ffsl_train_step followed by ffsl_set_update on the same stream, so both are
 run on identical copies of the state and must agree bit for bit (weights,
 indices, moments, bias, masks, exhausted count, loss and dX).  The oracle
-(train step, then SET) checks one case directly.  Shapes: one, two and four
-batch passes, the narrowest width (d = 128: a quarter of the draws meet a
+(train step, then SET) checks one case directly.  Shapes: one batch
+pass, batches of several tiles, the narrowest width (d = 128: a quarter of the draws meet a
 held column, so many rows are finished by the row-list SET kernel), a single
 sample, the largest number of pruned slots the fused path takes, and shapes
 where the library runs the two calls back to back (other widths, other
@@ -21,7 +21,9 @@ pytestmark = pytest.mark.gpu
 
 W1 = synth.WORKLOADS
 CASES = {
-    # fused: passes of 64 samples (1, 2 and 4), widths 768 and 128, B = 1
+    # fused: one pass of 64 samples, widths 768 and 128, B = 1 (c4s, mx128, b1);
+    # back to back over the staged sweep, B = 128 and 200 (c2s, mx200: the same
+    # two calls on both sides; several passes: test_gpu_mx_passes)
     "c4s": synth.scaled(W1["c4_bf16_L3M"], L=3001, name="c4s"),
     "c2s": synth.scaled(W1["c2_bf16_L131072"], L=2000, name="c2s"),
     "mx200": synth.scaled(W1["c4_bf16_L3M"], L=777, B=200, name="mx200"),

@@ -1,9 +1,9 @@
 """GPU parity of the squared hinge loss (FFSL_LOSS_SQHINGE) against the oracle on
 the same seeded inputs: forward and loss, the unfused backward, and the fused
-step on every sweep (fan-in 32 fast path in one and four batch passes, the
-wide fan-in 64 path, the general path in bf16 and fp32).  One case puts most
-labels past the margin, so that whole waves have zero dlogits and the fused
-paths skip their dW products."""
+step (the fused fan-in-32 path in one pass, the staged sweep in bf16 and fp32
+over one and several tiles; passes and the fused fan-in-64 path:
+test_gpu_wide).  One case puts most labels past the margin, so that whole waves
+have zero dlogits and the fused paths skip their dW products."""
 import numpy as np
 import pytest
 
