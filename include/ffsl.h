@@ -68,8 +68,8 @@ typedef enum {
  * "Hyperparameter Settings"), with signed targets yh = 2y - 1:
  *   loss = s * sum_{b,l} max(0, 1 - yh z)^2,   g = -2 s yh max(0, 1 - yh z).
  * g is exactly zero where yh z >= 1 (Sec. 2.2: the activation sparsity of a
- * hinge-like loss); the fused paths skip the dW products of a wave whose
- * dlogits are all zero.  Accepted by ffsl_forward_loss, ffsl_backward,
+ * hinge-like loss); the fused fan-in-32 and fan-in-64 paths skip the dW products
+ * of a wave whose dlogits are all zero.  Accepted by ffsl_forward_loss, ffsl_backward,
  * ffsl_train_step and ffsl_train_step_set. */
 #define FFSL_LOSS_SQHINGE 4u
 
@@ -199,9 +199,12 @@ FFSL_API int ffsl_backward(ffsl_layer *layer, const void *X, int32_t B,
 FFSL_API int ffsl_adam_step(ffsl_layer *layer, int64_t t, float lr, float beta1,
                    float beta2, float eps, float wd, void *stream);
 
-/* One fused training step: forward, BCE, dW, dbias, dX and Adam in one
- * streaming pass over the [L,k] arrays; the scores and dW never leave the
- * chip.  Same semantics as ffsl_forward_loss + ffsl_backward +
+/* One fused training step: forward, BCE, dW, dbias, dX and Adam, dW never
+ * leaving the chip.  The shapes of a fast path (bf16; fan-in 32, d a multiple of
+ * 128 up to 768, B <= 64; fan-in 64, d a multiple of 128 up to 2048, B <= 16) take
+ * one streaming pass over the [L,k] arrays, large layers of those shapes several
+ * for larger batches (see ffsl_workspace_bytes); the others pass the loss
+ * gradients of a slab of rows through the workspace.  Same semantics as ffsl_forward_loss + ffsl_backward +
  * ffsl_adam_step with the same arguments (up to fp32 rounding order); the
  * layer's dW/dbias buffers are neither needed nor written.  loss_out and
  * dX_out are nullable. */
@@ -323,9 +326,9 @@ FFSL_API int ffsl_set_update_threshold(ffsl_layer *layer, float tau, uint64_t se
 
 /* Measurement hook: while both events are non-null, every sweep call
  * (ffsl_forward_loss, ffsl_backward, ffsl_train_step) records `start`
- * (a hipEvent_t) on its stream right before its main sweep kernel and `stop`
- * right after it, so a caller can time that kernel alone with
- * hipEventElapsedTime.  Pass NULLs to turn it off.  The handle keeps the
+ * (a hipEvent_t) on its stream right before its main sweep kernel (its first
+ * slab's) and `stop` right after it (its last slab's), so a caller can time that
+ * part alone with hipEventElapsedTime.  Pass NULLs to turn it off.  The handle keeps the
  * event handles, not copies. */
 FFSL_API int ffsl_set_timing_events(ffsl_layer *layer, void *start, void *stop);
 

@@ -56,9 +56,15 @@ constexpr int WD_PASS_B = 16;   // samples per pass of the wide fan-in-64 fast p
 constexpr int WD_PASSES = 3;    // passes it takes at most
 // The fan-in-32 path takes larger batches in passes, each of which pays for its
 // own staging, first chunk and dX partial (about 50 us) but moves no loss
-// gradients through memory: below this many rows the staged sweep is faster
-// (131072 rows, B 128: 161 against 198 us; 262144: 276 against 287; 524288:
-// 591 against 483; fan-in 32, d 768)
+// gradients through memory: below this many rows the staged sweep is faster.
+// Staged time over passes' time at 2^16, 2^17, 2^18 and 2^19 rows:
+//   B 65    d 128: 0.85 0.90 0.92 1.05   d 384: 0.89 0.94 0.96 1.10   d 768: 0.83 0.93 1.01 1.16
+//   B 128   d 128: 0.69 0.77 0.83 0.98   d 384: 0.77 0.83 0.90 1.05   d 768: 0.69 0.79 0.89 1.10
+//   B 256   d 128: 0.92 0.89 0.89 0.91   d 384: 0.90 0.89 0.92 0.97   d 768: 0.76 0.81 0.86 0.99
+// B 96 and 192 lie between, B 512 and 1024 favour the staged sweep up to 2^20
+// rows (0.97 and less).  Passes still win by up to 4% in two places below the
+// line: a step with SET at 2^18 rows, d 768, B 65 (301 against 314 us), and B 256
+// at 2^10 rows, d up to 384 (42 against 43 us).
 constexpr int64_t MX_PASSES_MIN_L = ((int64_t)1 << 18) + 1;
 // layers whose shape the wide fan-in-64 fast path serves (bf16 values)
 inline bool wide_shape(int64_t L, int32_t d, int32_t k) {

@@ -506,7 +506,7 @@ __global__ __launch_bounds__(TK_THREADS) void k_topk_scan(TkArgs a) {
 //
 // What bounds it: the LDS gathers and their bank conflicts.  With rows loaded
 // by all 16 lanes instead (fan-in 64, width 2048, 1048576 labels, B 128, top
-// 5) the address units were busy 80% of the time and the scan took 846 us,
+// 5) the scan took 846 us,
 // against 692 with each value loaded once and crossed by DPP; lists that also
 // take the other workgroups' bests as bounds, four waves per SIMD and a short
 // merge take it to 572.  (The scan it replaced, each lane gathering its own
