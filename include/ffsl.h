@@ -133,7 +133,8 @@ FFSL_API size_t ffsl_workspace_bytes_ex(int64_t L, int32_t d, int32_t k, int32_t
  *   dW, dbias   [L,k] / [L] fp32 gradient buffers of the unfused path,
  *               nullable (then ffsl_backward/ffsl_adam_step are unavailable)
  *   workspace   device scratch of at least ffsl_workspace_bytes(...) bytes,
- *               256-byte aligned
+ *               256-byte aligned; workspace_bytes may be more, and all of it is
+ *               then the library's to use
  * The handle stores the pointers and shapes only; it owns no device memory.
  * Errors: FFSL_EINVAL for null required pointers, bad shapes or a short
  * workspace. */

@@ -506,12 +506,12 @@ __global__ __launch_bounds__(TK_THREADS) void k_topk_scan(TkArgs a) {
 //
 // What bounds it: the LDS gathers and their bank conflicts.  With rows loaded
 // by all 16 lanes instead (fan-in 64, width 2048, 1048576 labels, B 128, top
-// 5) the scan took 846 us,
-// against 692 with each value loaded once and crossed by DPP; lists that also
-// take the other workgroups' bests as bounds, four waves per SIMD and a short
-// merge take it to 572.  (The scan it replaced, each lane gathering its own
-// samples at two waves per SIMD: 1379.  Fan-in 32, width 768, 2812281 labels,
-// B 64: 424 -> 348.)
+// 5) the scan took 846 us, against 692 with each value loaded once and crossed
+// by DPP; lists that also take the other workgroups' bests as bounds, four waves
+// per SIMD and a short merge take it to 572, the VALU busy 65% of the time and
+// the LDS 56%, 63% of that bank conflicts.  (The scan it replaced, each lane
+// gathering its own samples at two waves per SIMD: 1379.  Fan-in 32, width 768,
+// 2812281 labels, B 64: 424 -> 348.)
 //
 // 1024 threads, four waves per SIMD, while the lists leave the registers for
 // them; past 20 keys a lane 512 threads.
