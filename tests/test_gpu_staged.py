@@ -83,14 +83,16 @@ def test_several_slabs_and_many_positives(torch_cuda, value):
 
 @pytest.mark.parametrize("value,k", [("bf16", 12), ("bf16", 100), ("f32", 12), ("f32", 40)])
 def test_repeated_columns_count_twice(torch_cuda, value, k):
-    """A column that a row holds more than once contributes every time."""
+    """A column that a row holds more than once contributes every time, whichever
+    of its weights are zero."""
     w = shape(value, 517, 300, k, 40)
     inp, bias = inputs(w, 5)
-    I = inp.I.copy()
+    I, Wb = inp.I.copy(), inp.W.copy()
     I[::3, 1] = I[::3, 0]
     I[::3, k - 1] = I[::3, 0]
     I[1::3, 9] = I[1::3, 8]
-    inp = synth.dataclasses.replace(inp, I=I)
+    Wb[::6, 0], Wb[::9, 1], Wb[::12, k - 1], Wb[1::6, 8], Wb[4::6, 9] = 0, 0, 0, 0, 0
+    inp = synth.dataclasses.replace(inp, I=I, W=Wb)
     note("staged repeated columns %s k=%d" % (value, k))
     layer, loss, dX, fwd, z = grads(torch_cuda, w, inp, bias)
     ref = oracle_grads(w, inp, bias, 1.0 / w.B)
